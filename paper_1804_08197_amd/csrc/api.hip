@@ -84,6 +84,7 @@ void free_all(Volume* v) {
   hipFree(v->pool);
   hipFree(v->page);
   hipFree(v->range);
+  if (v->bmax) hipFree(v->bmax);
   hipFree(v->empty);
   hipFree(v->info);
   hipFree(v->tf);
@@ -156,6 +157,7 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
   v->node_off[v->L] = nodes;
   v->nodes = nodes;
   v->M = d->layout == SG_LAYOUT_MICROBLOCK ? (v->S + 3) / 4 : 0;
+  v->Mb = (v->S + 3) / 4;
   const int64_t S3 = v->M ? (int64_t)v->M * v->M * v->M * 64 : (int64_t)v->S * v->S * v->Sx;
   v->slot_bytes = ((S3 * v->bpv + 64 + 255) / 256) * 256;
   v->entries = (int64_t)d->timepoints * d->channels * nodes;
@@ -176,7 +178,9 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
     v->bytes += (uint64_t)bytes;
     return true;
   };
-  const int64_t tf_bytes = (int64_t)kMaxChannels * (kMaxTfEntries + 1) * 16 + 2 * kMaxChannels * 8;
+  // transfer tables, domains and the skip tables beside them (launch_empty)
+  const int64_t tf_bytes = (int64_t)kMaxChannels * (kMaxTfEntries + 1) * 16 +
+                           2 * kMaxChannels * 8 + (int64_t)kMaxChannels * 2 * kMaxTfEntries * 4;
   bool ok = alloc((void**)&v->pool, pool_bytes) &&
             alloc((void**)&v->page, v->entries * 4) &&
             alloc((void**)&v->range, v->entries * 8) &&

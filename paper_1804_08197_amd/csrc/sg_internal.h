@@ -146,6 +146,7 @@ struct Volume {
   int S = 0;         // stored edge B + 2
   int Sx = 0;        // row stride in voxels (S rounded up to kRowAlignBytes)
   int M = 0;         // SG_LAYOUT_MICROBLOCK: 4^3 blocks per slot edge; 0: linear
+  int Mb = 0;        // 4^3 blocks per slot edge in either layout: ceil(S / 4)
   int L = 0;         // levels
   int32_t ldims[kMaxLevels][3]{};
   int32_t grid[kMaxLevels][3]{};
@@ -157,6 +158,9 @@ struct Volume {
   uint8_t* pool = nullptr;    // [slots][S^3] voxels
   int32_t* page = nullptr;    // [T][C][nodes] -> slot, -1 if not resident
   uint32_t* range = nullptr;  // [T][C][nodes][2] min, max of stored voxels
+  uint8_t* bmax = nullptr;    // [slots][Mb^3] largest voxel of each 4^3 block
+                              // of a slot (blocks x fastest), or NULL
+  int64_t bmax_stride = 0;    // bytes per slot of bmax
   uint8_t* empty = nullptr;   // [T][nodes] bit 0: every channel transparent,
                               // bit 1: every channel emits nothing
   NodeInfo* info = nullptr;   // [nodes]
@@ -232,8 +236,8 @@ sg_status launch_upload(Volume* v, int c, int t, int level, int n,
                         hipStream_t s);
 sg_status launch_downsample(Volume* v, int c, int t, int level_dst,
                             hipStream_t s);
-sg_status launch_apron(Volume* v, int c, int t, hipStream_t s);
-sg_status launch_range(Volume* v, int c, int t, hipStream_t s);
+// Aprons, block maxima and value ranges of one (channel, timepoint).
+sg_status launch_commit(Volume* v, int c, int t, hipStream_t s);
 sg_status launch_empty(Volume* v, hipStream_t s);
 // Cache volumes: every top-level node resident at timepoint t?
 bool top_level_resident(const Volume* v, int t);
