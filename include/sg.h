@@ -81,8 +81,11 @@ enum {
   SG_SKIP_EMPTY = 1u << 1, /* skip nodes that cannot contribute: zero opacity
                               (emission-absorption), zero emission
                               (emission-only), a stored maximum no larger than
-                              the ray's running maxima (maximum intensity);
-                              the image is the same either way              */
+                              the ray's running maxima (maximum intensity),
+                              and, inside a node, the staged kernel's slabs
+                              that hold no extinction (emission); the image
+                              is the same either way (instrumented renders
+                              sample and count every slab of a node)        */
   SG_GATHER = 1u << 2      /* tuning/testing: trilinear stencils read the brick
                               pool directly instead of LDS-staged brick tiles;
                               the image is bit-identical either way          */

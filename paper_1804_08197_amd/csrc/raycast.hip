@@ -110,6 +110,22 @@ float ert_transmittance(float ert) {
 }
 
 
+// Does a sample without extinction leave everything as it is? Not when it
+// would terminate a ray that is still clear (ert <= 0) or set its depth
+// (depth_alpha <= 0).
+bool clear_samples_idle(const sg_render_params* p, float t_ert) {
+  return !(t_ert >= 1.0f) && p->depth_alpha > 0.0;
+}
+// May a whole slab be stepped over? Its samples' ray parameters must add up
+// exactly, since one multiply-add takes the place of their sum: (k + 1/2)
+// step is exact in FP32 for every k of a segment (fewer than 2^15 samples)
+// when the step has at most 8 significant bits.
+bool step_adds_up(double step) {
+  int e = 0;
+  const double m = std::frexp(step, &e) * 256.0;
+  return m == std::floor(m);
+}
+
 // Arguments shared by the stream path and the graph path.
 void fill_args(const Volume* v, const sg_render_params* params, int n_views,
                const ViewDev* dviews, const int32_t* cutmap, int64_t blocks,
@@ -132,9 +148,7 @@ void fill_args(const Volume* v, const sg_render_params* params, int n_views,
   for (int L = 0; L < v->L; ++L)
     for (int i = 0; i < 3; ++i) a.ldims[L][i] = v->ldims[L][i];
   for (int c = 0; c < C; ++c) {
-    const double sc = (double)(v->tf_n - 1) / (v->tf_hi[c] - v->tf_lo[c]);
-    a.tf_scale[c] = (float)sc;
-    a.tf_bias[c] = (float)(-v->tf_lo[c] * sc);
+    tf_window(v, c, &a.tf_scale[c], &a.tf_bias[c]);
   }
   for (int i = 0; i < 4; ++i) a.bg[i] = (float)params->background[i];
   int key_levels = 0;
@@ -176,6 +190,12 @@ void fill_args(const Volume* v, const sg_render_params* params, int n_views,
   a.t_ert = ert_transmittance(a.ert);
   a.depth_alpha = (float)params->depth_alpha;
   a.model = params->model;
+  if (a.skip_empty && step_adds_up(params->step_voxels) &&
+      (params->model != SG_MODEL_EMISSION_ABSORPTION || clear_samples_idle(params, a.t_ert)))
+    a.bmax = v->bmax;
+  a.Mb = v->Mb;
+  a.dim = reinterpret_cast<const int32_t*>(reinterpret_cast<const uint8_t*>(v->tf) +
+                                           tf_layout(C, v->tf_n).dim);
   a.n_planes = params->n_planes;
   a.roi_on = params->roi_on;
   for (int j = 0; j < 4; ++j)

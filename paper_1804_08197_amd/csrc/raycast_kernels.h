@@ -391,8 +391,11 @@ __device__ __forceinline__ void next_segment(Ray& r, const RenderArgs& a, const 
 #pragma unroll
     for (int i = 0; i < 3; ++i) r.b[i] = ni.b[i];
     // skipped nodes are dropped before any box arithmetic
+    uint32_t loud = 0;  // 1: every block of some channel counts (see quiet)
     if (MODEL != kModelMip) {
-      if (a.skip_empty && (a.empty[r.node] & (MODEL == kModelEmission ? 2 : 1))) continue;
+      const uint32_t f = (uint32_t)a.empty[r.node] >> (MODEL == kModelEmission ? 1 : 0);
+      if (a.skip_empty && (f & 1)) continue;
+      loud = (f >> 2) & 1;
     } else if (a.skip_empty && r.sampled) {
       bool raise = false;
 #pragma unroll
@@ -416,6 +419,7 @@ __device__ __forceinline__ void next_segment(Ray& r, const RenderArgs& a, const 
     if (t1 > r.tf) t1 = r.tf;
     if (!(t0 < t1)) continue;
     r.key = visibility_key(a.key_levels, a.B, e, r.L, r.b);
+    if (MODEL != kModelMip) r.key = (r.key << 1) | (a.bmax ? loud ^ 1 : 0);
     r.t0 = t0;
     r.t1 = t1;
     // sampling frame: stored index of the brick, FP32 from an FP64 origin
@@ -1167,6 +1171,71 @@ __device__ __forceinline__ void stat_loop(const RenderArgs& a, int taken, bool p
   if (pool && taken > 0) atomicAdd((unsigned long long*)a.counters + 6, (unsigned long long)taken);
 }
 
+// Can any voxel of the region o .. o + wd - 1 of a node change a ray? From
+// the largest voxel of each 4x4x4 block that the region meets (one load per
+// block): yes when a block of some channel exceeds the channel's largest
+// value without extinction (emission-absorption) or colour (emission-only).
+// A trilinear value never exceeds its largest voxel and the table index
+// never falls as the value rises, so a slab that does not count leaves every
+// accumulator as it is, bit for bit. (Not used under maximum intensity: a
+// slab must lie below the running maxima of all the wave's rays, which paid
+// for the tests at best, 624 against 633 us on a 2 x 1080x1200 frame.)
+// Called by the whole wave; slot (the node's pool slots, whose block maxima
+// lie at a fixed fraction of their offset), o and wd are the same in every
+// lane.
+//
+// The arguments that only this test needs are read anew at each test, from
+// the kernel's argument segment through a pointer the compiler cannot see
+// through: hoisted out of the slab loop they would live in scalar registers
+// across the sample loops, and the spills of those take vector registers
+// (the three-channel kernel: 121 -> 171 VGPRs; they also sit at the end of
+// RenderArgs, since moving the other arguments over cache lines cost the
+// other kernels 2.5%).
+//
+// Thin tubes in a 1024^3 uint16 volume, stereo 1440x1600: 2557 -> 1364 us;
+// three channels of 1024x1024x512 cells: 6991 -> 4063 us; noise everywhere
+// (no node is quiet): 518 -> 520 us. Also skipping the table of a sample
+// whose value is transparent in every lane (a ballot and a branch per
+// channel) cost more than it saved: 1378 -> 1426, 4496 -> 4741 us.
+template <typename T, int CH, int MODEL, bool MB>
+__device__ __forceinline__ bool slab_counts(const T* const (&slot)[CH], const int o[3],
+                                            const int wd[3]) {
+  typedef __attribute__((address_space(4))) const RenderArgs* Args;
+  Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  const int x0 = o[0] >> 2, y0 = o[1] >> 2, z0 = o[2] >> 2;
+  const int nx = ((o[0] + wd[0] - 1) >> 2) - x0 + 1, ny = ((o[1] + wd[1] - 1) >> 2) - y0 + 1,
+            nz = ((o[2] + wd[2] - 1) >> 2) - z0 + 1;
+  const int nxy = nx * ny, nb = nxy * nz, Mb = a->Mb;
+  // (exact: see brick_rows.h's quot_exact; nb < 2^13)
+  const float inv_x = __builtin_amdgcn_rcpf((float)nx), inv_xy = __builtin_amdgcn_rcpf((float)nxy);
+  const int base = (z0 * Mb + y0) * Mb + x0;
+  // (whole maxima, and a loop whose trip count and lanes do not vary: masks
+  // kept per channel would be spilled)
+  int mx[CH];
+#pragma unroll
+  for (int ch = 0; ch < CH; ++ch) mx[ch] = 0;
+  for (int p0 = 0; p0 < nb; p0 += 64) {
+    const int p = min(p0 + (int)(threadIdx.x & 63), nb - 1);
+    const int z = (int)(((float)p + 0.5f) * inv_xy), t = p - z * nxy,
+              y = (int)(((float)t + 0.5f) * inv_x), x = t - y * nx;
+    const int i = base + (z * Mb + y) * Mb + x;
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) {
+      const T* bm = reinterpret_cast<const T*>(
+          a->bmax + ((reinterpret_cast<const uint8_t*>(slot[ch]) - a->pool) >> bmax_shift(MB)));
+      mx[ch] = max(mx[ch], (int)bm[i]);
+    }
+  }
+  // (a table that no kernel writes while a render runs: scalar loads)
+  typedef __attribute__((address_space(4))) const int32_t* Table;
+  int over = -1;  // the largest excess over a channel's limit
+#pragma unroll
+  for (int ch = 0; ch < CH; ++ch)
+    over = max(over, mx[ch] - ((Table)a->dim)[2 * ch + (MODEL == kModelEmission)]);
+  return __ballot(over > 0) != 0;
+}
+
 // One wave tile of the staged kernel (the whole wave active).
 template <typename T, int CH, bool STATS, int MODEL, bool MB>
 __device__ __forceinline__ void staged_tile(const RenderArgs& a, const float4* s_tf, T* stage,
@@ -1196,7 +1265,6 @@ __device__ __forceinline__ void staged_tile(const RenderArgs& a, const float4* s
   const int B = a.B, S = a.S, Sx = a.Sx;
   // the wave's rays belong to one view: its depth request is wave-uniform
   const bool depth_on = uniform(V.depth ? 1 : 0) != 0;
-
   while (true) {
     // --- the wave's next node: smallest front-to-back key among its rays
     const uint64_t K = wave_min_u64(r.alive ? r.key : ~0ull);
@@ -1214,6 +1282,9 @@ __device__ __forceinline__ void staged_tile(const RenderArgs& a, const float4* s
           (uint64_t)(uint32_t)uniform((int)(uint32_t)p) |
           ((uint64_t)(uint32_t)uniform((int)(uint32_t)(p >> 32)) << 32));
     }
+    // may a slab of the node hold nothing that counts? (the key's lowest bit;
+    // scenes without empty space then pay for no test)
+    const bool quiet = !STATS && MODEL != kModelMip && (K & 1) != 0;
     if (STATS) {
       const uint64_t alive = __ballot(r.alive);
       if (lane == 0) {
@@ -1374,7 +1445,17 @@ __device__ __forceinline__ void staged_tile(const RenderArgs& a, const float4* s
         o[i] = uniform(o[i]);
         wd[i] = uniform(wd[i]);
       }
-      if (fits) {
+      // --- can the slab change a ray at all?
+      const bool counts = STATS || !fits || !quiet ||
+                          slab_counts<T, CH, MODEL, MB>(slot, o, wd);
+      if (!counts) {
+        // nothing in the region can change a ray: its samples are stepped
+        // over (the sum is exact, see step_adds_up)
+        if (kb >= r.k) {
+          r.tau = fmaf((float)(kb + 1 - r.k), r.Df, r.tau);
+          r.k = kb + 1;
+        }
+      } else if (fits) {
         // --- stage the region of every channel straight from the pool into
         // LDS (global_load_lds: lane i of an instruction writes chunk i after
         // the instruction's LDS base). The region is wd[1] * wd[2] rows of

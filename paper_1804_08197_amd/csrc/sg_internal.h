@@ -79,7 +79,8 @@ struct NodeInfo {
 // root of key_levels levels over the volume, each child index flipped so
 // that the child on the eye's side of each splitting plane comes first.
 // Nodes of a cut sorted by this key are in front-to-back order for every ray
-// from e (the order in which Sec 5.2 renders its blocks).
+// from e (the order in which Sec 5.2 renders its blocks). Below 2^60: at most
+// 20 levels (edges of at most 2^20 voxels).
 __device__ __forceinline__ uint64_t visibility_key(int key_levels, int B, const double e[3],
                                                    int L, const int b[3]) {
   uint64_t key = 0;
@@ -138,6 +139,11 @@ __host__ __device__ __forceinline__ int64_t slot_index(int x, int y, int z, int 
          ((y & 3) << 2) + (x & 3);
 }
 
+// The block maxima of a slot at byte p of the pool lie at byte p >> bmax_shift
+// of Volume::bmax: Mb^3 voxels in 1/64 of a micro-block slot (Mb^3 blocks of
+// 64 voxels), in 1/32 of a linear one (S^3 voxels and padding; Mb = ceil(S / 4)).
+__host__ __device__ constexpr int bmax_shift(bool micro) { return micro ? 6 : 5; }
+
 struct Volume {
   sg_volume_desc d{};
   int bpv = 0;       // bytes per voxel
@@ -160,9 +166,12 @@ struct Volume {
   uint32_t* range = nullptr;  // [T][C][nodes][2] min, max of stored voxels
   uint8_t* bmax = nullptr;    // [slots][Mb^3] largest voxel of each 4^3 block
                               // of a slot (blocks x fastest), or NULL
-  int64_t bmax_stride = 0;    // bytes per slot of bmax
+  int64_t bmax_stride = 0;    // bytes per slot of bmax (slot_bytes >> bmax_shift)
+  uint32_t* dark = nullptr;   // [T][C][nodes] smallest of a brick's block maxima
   uint8_t* empty = nullptr;   // [T][nodes] bit 0: every channel transparent,
-                              // bit 1: every channel emits nothing
+                              // bit 1: every channel emits nothing, bits 2
+                              // and 3: no 4^3 block of some channel is
+                              // transparent (emits nothing)
   NodeInfo* info = nullptr;   // [nodes]
   float* tf = nullptr;        // [C][tf_n + 1][4] (last entry repeated)
   int tf_n = 0;
@@ -239,6 +248,26 @@ sg_status launch_downsample(Volume* v, int c, int t, int level_dst,
 // Aprons, block maxima and value ranges of one (channel, timepoint).
 sg_status launch_commit(Volume* v, int c, int t, hipStream_t s);
 sg_status launch_empty(Volume* v, hipStream_t s);
+// Byte offsets in Volume::tf of what follows the tables: the domains, the
+// skip flags' tables (see empty_kernel), RenderArgs::dim.
+struct TfLayout {
+  int64_t lohi, next, dim, bytes;
+};
+inline TfLayout tf_layout(int C, int n) {
+  TfLayout t;
+  t.lohi = (int64_t)C * (n + 1) * 4 * (int64_t)sizeof(float);
+  t.next = t.lohi + 2 * C * (int64_t)sizeof(double);
+  t.dim = t.next + (int64_t)C * 2 * n * (int64_t)sizeof(int32_t);
+  t.bytes = t.dim + (int64_t)C * 2 * (int64_t)sizeof(int32_t);
+  return t;
+}
+// A channel's transfer-table window in the ray caster's FP32: the table
+// index of value x is fma(x, scale, bias).
+inline void tf_window(const Volume* v, int c, float* scale, float* bias) {
+  const double sc = (double)(v->tf_n - 1) / (v->tf_hi[c] - v->tf_lo[c]);
+  *scale = (float)sc;
+  *bias = (float)(-v->tf_lo[c] * sc);
+}
 // Cache volumes: every top-level node resident at timepoint t?
 bool top_level_resident(const Volume* v, int t);
 sg_status commit(Volume* v, hipStream_t s);
@@ -338,6 +367,13 @@ struct RenderArgs {
   double planes[4][4];  // plane j keeps (n . p) + w <= 0: (nx, ny, nz, w)
   double roi[6];        // region of interest lo xyz, hi xyz
   const int32_t* enable;  // NULL, or a device flag: 0 = every workgroup returns at once
+  // slabs that cannot contribute are passed over (staged kernel): the block
+  // maxima (Volume::bmax; NULL: every slab is sampled) and, per channel, the
+  // largest voxel value without extinction and without colour (dim[c][2],
+  // -1: none; refreshed with the transfer tables)
+  const uint8_t* bmax;
+  const int32_t* dim;
+  int32_t Mb;
 };
 
 // The ray-casting launch (kernel, grid, LDS) for arguments `a`; a.grid is

@@ -11,6 +11,7 @@
 // in a GPU cache). With the apron, any trilinear sample inside a node reads
 // only that node's slot.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 
 #include "brick_rows.h"
@@ -193,7 +194,8 @@ __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t 
 template <typename T, bool MB>
 __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_bytes,
                                                     const int32_t* page, const NodeInfo* info,
-                                                    Levels lv, uint32_t* range, int per, int logB,
+                                                    Levels lv, uint32_t* range,
+                                                    uint32_t* dark, int per, int logB,
                                                     int S, int Sx, int M) {
   const int64_t node = blockIdx.x / (unsigned)per;
   const int part = (int)(blockIdx.x % (unsigned)per);
@@ -217,6 +219,7 @@ __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_
   if (part == 0 && threadIdx.x == 0) {
     range[2 * node] = 0xFFFFFFFFu;
     range[2 * node + 1] = 0u;
+    dark[node] = 0xFFFFFFFFu;
   }
   // stored voxel (x, y, z) of this brick from the brick that owns it
   auto from = [&](int x, int y, int z) -> const T* {
@@ -266,7 +269,7 @@ __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_
 template <typename T, bool MB>
 __global__ __launch_bounds__(256) void range_kernel(const uint8_t* __restrict__ pool,
                                                     int64_t slot_bytes, const int32_t* page,
-                                                    uint32_t* range, uint8_t* bmax,
+                                                    uint32_t* range, uint32_t* dark, uint8_t* bmax,
                                                     int64_t bmax_stride, int per, int S, int Sx,
                                                     int M) {
   const int64_t node = blockIdx.x / (unsigned)per;
@@ -275,7 +278,7 @@ __global__ __launch_bounds__(256) void range_kernel(const uint8_t* __restrict__ 
   const int32_t slot = page[node];
   const T* own = reinterpret_cast<const T*>(pool + (int64_t)slot * slot_bytes);
   T* bm = bmax ? reinterpret_cast<T*>(bmax + (int64_t)slot * bmax_stride) : nullptr;
-  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u, dk = 0xFFFFFFFFu;
   // (the same trip count for every lane: blocks are folded across lanes)
   for (int i0 = part * 256 * kRowBatch; i0 < items; i0 += per * 256 * kRowBatch) {
     Row w[kRowBatch];
@@ -296,10 +299,11 @@ __global__ __launch_bounds__(256) void range_kernel(const uint8_t* __restrict__ 
       if (on[u]) row_range(o[u], S - w[u].x, lo, rmax);
       hi = max(hi, rmax);
       rmax = row16_max(rmax);
+      if (i < items) dk = min(dk, rmax);
       if (bm && i < items && (i & 15) == 0) bm[i >> 4] = (T)rmax;
     }
   }
-  range_out(lo, hi, range + 2 * node, per == 1);
+  range_out(lo, hi, dk, range + 2 * node, dark + node, per == 1);
 }
 
 // Skip flags (one thread per (timepoint, node)). Bit 0 (transparent): for
@@ -310,15 +314,20 @@ __global__ __launch_bounds__(256) void range_kernel(const uint8_t* __restrict__ 
 // whose index is rounded in single precision. next[c][0][k] / next[c][1][k]:
 // the first entry from k on with extinction / with colour (tf_n: none), so
 // a node takes two reads instead of a walk over the entries (38 -> 3.4 us
-// for 585 nodes and 256 entries).
-__global__ void empty_kernel(const uint32_t* range, const int32_t* next, int tf_n,
-                             const double* lo, const double* hi, int C,
+// for 585 nodes and 256 entries). Bits 2 and 3: some channel's every 4x4x4
+// block reaches above the largest value without extinction (colour), so no
+// slab of the node can be passed over.
+__global__ void empty_kernel(const uint32_t* range, const uint32_t* dark, const int32_t* next,
+                             const int32_t* dim, int tf_n, const double* lo, const double* hi, int C,
                              int64_t nodes, int64_t total, uint8_t* empty) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
     int64_t t = i / nodes, node = i - t * nodes;
-    bool clear = true, dark = true;
+    bool clear = true, unlit = true, no_clear = false, no_unlit = false;
     for (int c = 0; c < C; ++c) {
+      const int64_t dk = dark[(t * C + c) * nodes + node];
+      no_clear |= dk > dim[2 * c];
+      no_unlit |= dk > dim[2 * c + 1];
       const uint32_t* r = range + 2 * ((t * C + c) * nodes + node);
       double umin = (((double)r[0] - lo[c]) / (hi[c] - lo[c])) * (double)(tf_n - 1);
       double umax = (((double)r[1] - lo[c]) / (hi[c] - lo[c])) * (double)(tf_n - 1);
@@ -329,9 +338,10 @@ __global__ void empty_kernel(const uint32_t* range, const int32_t* next, int tf_
       const int32_t* nx = next + (int64_t)c * 2 * tf_n;
       // (an empty interval, khi < klo: nothing can show)
       if (nx[klo] <= khi) clear = false;
-      if (nx[tf_n + klo] <= khi) dark = false;
+      if (nx[tf_n + klo] <= khi) unlit = false;
     }
-    empty[i] = (uint8_t)((clear ? 1 : 0) | (dark ? 2 : 0));
+    empty[i] = (uint8_t)((clear ? 1 : 0) | (unlit ? 2 : 0) | (no_clear ? 4 : 0) |
+                         (no_unlit ? 8 : 0));
   }
 }
 
@@ -406,7 +416,8 @@ sg_status launch_downsample(Volume* v, int c, int t, int level_dst,
 }
 
 sg_status launch_commit(Volume* v, int c, int t, hipStream_t s) {
-  uint32_t* r = v->range + 2 * ((int64_t)t * v->d.channels + c) * v->nodes;
+  const int64_t first = ((int64_t)t * v->d.channels + c) * v->nodes;
+  uint32_t *r = v->range + 2 * first, *dk = v->dark + first;
   Levels lv{};
   for (int L = 0; L < v->L; ++L) {
     for (int a = 0; a < 3; ++a) {
@@ -420,9 +431,9 @@ sg_status launch_commit(Volume* v, int c, int t, hipStream_t s) {
 #define SG_COMMIT(T, MB)                                                                       \
   do {                                                                                         \
     hipLaunchKernelGGL((apron_kernel<T, MB>), grid, dim3(256), 0, s, v->pool, v->slot_bytes,   \
-                       page_at(v, c, t), v->info, lv, r, per, v->logB, v->S, v->Sx, v->Mb);    \
+                       page_at(v, c, t), v->info, lv, r, dk, per, v->logB, v->S, v->Sx, v->Mb);    \
     hipLaunchKernelGGL((range_kernel<T, MB>), grid, dim3(256), 0, s, v->pool, v->slot_bytes,   \
-                       page_at(v, c, t), r, v->bmax, v->bmax_stride, per, v->S, v->Sx, v->Mb); \
+                       page_at(v, c, t), r, dk, v->bmax, v->bmax_stride, per, v->S, v->Sx, v->Mb); \
   } while (0)
   if (v->bpv == 1) {
     if (v->M) SG_COMMIT(uint8_t, true); else SG_COMMIT(uint8_t, false);
@@ -434,16 +445,27 @@ sg_status launch_commit(Volume* v, int c, int t, hipStream_t s) {
   return SG_OK;
 }
 
+// The largest voxel value whose table index fma(x, scale, bias) is at most
+// `last` (-1: none): the index never falls as the value rises.
+static int32_t largest_below(float scale, float bias, float last, int32_t top) {
+  if (!std::isfinite(scale) || !std::isfinite(bias) || !(bias <= last)) return -1;
+  int32_t lo = 0, hi = top;  // fma(lo) <= last
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) / 2;
+    if (std::fmaf((float)mid, scale, bias) <= last) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
 sg_status launch_empty(Volume* v, hipStream_t s) {
   const int C = v->d.channels, n = v->tf_n;
   // tables: TF [C][n+1][4] floats, then lo[C], hi[C] doubles, then
-  // next[C][2][n] (see empty_kernel)
-  std::vector<uint8_t> blob;
-  const int64_t tf_bytes = (int64_t)C * (n + 1) * 4 * sizeof(float);
-  const int64_t next_at = tf_bytes + 2 * C * (int64_t)sizeof(double);
-  blob.resize((size_t)(next_at + (int64_t)C * 2 * n * (int64_t)sizeof(int32_t)));
+  // next[C][2][n] (see empty_kernel), then dim[C][2] (see RenderArgs)
+  const TfLayout at = tf_layout(C, n);
+  std::vector<uint8_t> blob((size_t)at.bytes);
   float* f = reinterpret_cast<float*>(blob.data());
-  int32_t* next = reinterpret_cast<int32_t*>(blob.data() + next_at);
+  int32_t* next = reinterpret_cast<int32_t*>(blob.data() + at.next);
+  int32_t* dim = reinterpret_cast<int32_t*>(blob.data() + at.dim);
   for (int c = 0; c < C; ++c) {
     const std::vector<float>& h = v->tf_host[c];
     float* o = f + (int64_t)c * (n + 1) * 4;
@@ -451,14 +473,23 @@ sg_status launch_empty(Volume* v, hipStream_t s) {
     std::memcpy(o + 4 * n, h.data() + 4 * (n - 1), 4 * sizeof(float));
     int32_t* nx = next + (int64_t)c * 2 * n;
     int32_t opaque = n, bright = n;
+    bool tame = true;  // differences of entries stay finite
     for (int k = n - 1; k >= 0; --k) {
       if (h[4 * k + 3] != 0.0f) opaque = k;
       if (h[4 * k] != 0.0f || h[4 * k + 1] != 0.0f || h[4 * k + 2] != 0.0f) bright = k;
       nx[k] = opaque;
       nx[n + k] = bright;
+      for (int q = 0; q < 4; ++q) tame = tame && std::fabs(h[4 * k + q]) < 1e37f;
     }
+    // up to the last entry before the first one with extinction (colour),
+    // every interpolated value is exactly zero
+    float scale, bias;
+    tf_window(v, c, &scale, &bias);
+    const int32_t top = v->bpv == 1 ? 255 : 65535;
+    dim[2 * c] = tame && opaque > 0 ? largest_below(scale, bias, (float)(opaque - 1), top) : -1;
+    dim[2 * c + 1] = tame && bright > 0 ? largest_below(scale, bias, (float)(bright - 1), top) : -1;
   }
-  double* lohi = reinterpret_cast<double*>(blob.data() + tf_bytes);
+  double* lohi = reinterpret_cast<double*>(blob.data() + at.lohi);
   for (int c = 0; c < C; ++c) {
     lohi[c] = v->tf_lo[c];
     lohi[C + c] = v->tf_hi[c];
@@ -466,11 +497,12 @@ sg_status launch_empty(Volume* v, hipStream_t s) {
   sg_status st = stage_to_device(v, blob.data(), (int64_t)blob.size(), v->tf, s);
   if (st != SG_OK) return st;
   const uint8_t* dev = reinterpret_cast<const uint8_t*>(v->tf);
-  const double* dlo = reinterpret_cast<const double*>(dev + tf_bytes);
-  const int32_t* dnext = reinterpret_cast<const int32_t*>(dev + next_at);
+  const double* dlo = reinterpret_cast<const double*>(dev + at.lohi);
+  const int32_t* dnext = reinterpret_cast<const int32_t*>(dev + at.next);
+  const int32_t* ddim = reinterpret_cast<const int32_t*>(dev + at.dim);
   int64_t total = (int64_t)v->d.timepoints * v->nodes;
-  hipLaunchKernelGGL(empty_kernel, dim3(blocks_for(total)), dim3(256), 0, s, v->range, dnext, n,
-                     dlo, dlo + C, C, v->nodes, total, v->empty);
+  hipLaunchKernelGGL(empty_kernel, dim3(blocks_for(total)), dim3(256), 0, s, v->range, v->dark,
+                     dnext, ddim, n, dlo, dlo + C, C, v->nodes, total, v->empty);
   SG_HIP(hipGetLastError());
   return SG_OK;
 }
