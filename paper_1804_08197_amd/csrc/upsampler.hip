@@ -46,9 +46,9 @@ constexpr int kCh = 32;       // output channels of every layer
 constexpr int kUsed = 20;     // used output channels of the last layer
 
 // packed weights: per layer w[9][cin][32] then b[32]
-constexpr int64_t layer_size(int l) { return (int64_t)9 * kCin[l] * kCh + kCh; }
+__host__ __device__ constexpr int64_t layer_size(int l) { return (int64_t)9 * kCin[l] * kCh + kCh; }
 constexpr int64_t kParams = layer_size(0) + layer_size(1) + layer_size(2) + layer_size(3);
-int64_t layer_off(int l) {
+constexpr int64_t layer_off(int l) {
   int64_t o = 0;
   for (int i = 0; i < l; ++i) o += layer_size(i);
   return o;
@@ -105,89 +105,158 @@ enum { kReluBf16 = 0, kBiasF32 = 1, kMaskBf16 = 2 };
 // y[p][co] = bias[co] + sum_{tap, ci} x[p + off(tap)][ci] * w[tap][ci][co]
 // (the bias is the accumulator's starting value; the sum runs in K order),
 // then the epilogue; zero padding, for N images of H x W. wt: packed
-// [K / 8][32][8] bf16. A wave computes 64 pixels (two blocks of 32) x 32
-// channels as the transposed product: A = weights (32 channels x 16 K),
-// B = pixels (16 K x 32 pixels).
+// [K / 8][32][8] bf16. The transposed product of a 32-pixel row piece: A =
+// weights (32 channels x 16 K), B = pixels (16 K x 32 pixels).
+//
+// A wave walks down a column of row pieces. The weights stay in registers,
+// and with 32 input channels so do the pixels of the three rows in reach (at
+// the three column shifts, two 8-channel groups each): a row piece costs six
+// 16-byte loads per lane instead of eighteen. Bound by memory: a layer reads
+// and writes 64 bytes per pixel.
+// The wave's share: row pieces [s0, s1) of the N ceil(W / 32) H pieces,
+// counted down the columns.
+constexpr int kPiece = 32;
+struct Pieces {
+  int64_t s0, s1;
+  int cols;  // row pieces per image row
+};
+__device__ __forceinline__ Pieces wave_pieces(int N, int H, int W, int width) {
+  Pieces p;
+  p.cols = (W + width - 1) / width;
+  const int64_t all = (int64_t)N * p.cols * H;
+  const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+  // (the wave's number in a scalar register: rows and their addresses then are)
+  const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) +
+                    __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t per = (all + waves - 1) / waves;
+  p.s0 = w * per < all ? w * per : all;
+  p.s1 = p.s0 + per < all ? p.s0 + per : all;
+  return p;
+}
+
+template <int EPI>
+__device__ __forceinline__ void conv_store(const floatx16& acc, int64_t p, int half, void* out,
+                                           const bf16* mask) {
+  // channels acc_channel(4 g + i, half) = 8 g + 4 half + i, four consecutive per g
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int c = 8 * g + 4 * half;
+    if (EPI == kBiasF32) {
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + p * kCh + c) =
+          make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+    } else {
+      float r[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[i] = acc[4 * g + i];
+      if (EPI == kReluBf16) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = fmaxf(r[i], 0.0f);
+      } else {
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        const bf16x4 m = *reinterpret_cast<const bf16x4*>(mask + p * kCh + c);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = bf(m[i]) > 0.0f ? r[i] : 0.0f;
+      }
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(out) + p * kCh + c) = pack4(r);
+    }
+  }
+}
+
 template <int CIN, int EPI>
-__global__ __launch_bounds__(256) void conv_kernel(const bf16* __restrict__ x, int N, int H, int W,
-                                                   const bf16x8* __restrict__ wt,
-                                                   const float* __restrict__ bias,
-                                                   void* __restrict__ out,
-                                                   const bf16* __restrict__ mask) {
-  const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
-  const int64_t P = (int64_t)N * H * W;
-  const int64_t p0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
-  if (p0 >= P) return;  // whole wave
-  // the lane's pixel in each of the two blocks
-  int py[2], px[2], pn[2];
-  bool pv[2];
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    const int64_t p = p0 + mb * 32 + col;
-    pv[mb] = p < P;
-    const int64_t q = pv[mb] ? p : 0;
-    pn[mb] = (int)(q / ((int64_t)H * W));
-    const int r = (int)(q - (int64_t)pn[mb] * H * W);
-    py[mb] = r / W;
-    px[mb] = r - py[mb] * W;
-  }
-  // the bias is the accumulators' starting value (no bias: 0); register r
-  // holds channel acc_channel(r, half)
-  floatx16 acc[2];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float b = EPI == kMaskBf16 ? 0.f : bias[acc_channel(r, half)];
-    acc[0][r] = b;
-    acc[1][r] = b;
-  }
+__global__ __launch_bounds__(256, 2) void conv_kernel(const bf16* __restrict__ x, int N, int H,
+                                                      int W, const bf16x8* __restrict__ wt,
+                                                      const float* __restrict__ bias,
+                                                      void* __restrict__ out,
+                                                      const bf16* __restrict__ mask) {
   constexpr int KSTEPS = ksteps(CIN);
+  const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+  const Pieces pc = wave_pieces(N, H, W, kPiece);
+  if (pc.s0 >= pc.s1) return;  // whole wave
   const bf16x8 zero8 = {(bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f,
                         (bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f};
-#pragma unroll 1
-  for (int s = 0; s < KSTEPS; ++s) {
-    const int k8 = 2 * s + half;  // this lane's group of 8 K values
-    const int tap = CIN == 32 ? k8 >> 2 : k8;
-    const int c0 = CIN == 32 ? (k8 & 3) * 8 : 0;
-    const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-    bf16x8 a[2];
+  bf16x8 wf[KSTEPS];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      const int yy = py[mb] + dy, xx = px[mb] + dx;
-      const bool in = pv[mb] && tap < 9 && yy >= 0 && yy < H && xx >= 0 && xx < W;
-      a[mb] = in ? *reinterpret_cast<const bf16x8*>(
-                       x + (((int64_t)pn[mb] * H + yy) * W + xx) * CIN + c0)
-                 : zero8;
-    }
-    const bf16x8 w = wt[(int64_t)k8 * kCh + col];
+  for (int s = 0; s < KSTEPS; ++s) wf[s] = wt[(int64_t)(2 * s + half) * kCh + col];
+  // the bias is the accumulators' starting value (no bias: 0); register r
+  // holds channel acc_channel(r, half)
+  floatx16 start;
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-      acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a[mb], acc[mb], 0, 0, 0);
-  }
-  // lane: pixel p0 + 32 mb + col; channels acc_channel(4 g + i, half) =
-  // 8 g + 4 half + i, four consecutive per g
+  for (int r = 0; r < 16; ++r) start[r] = EPI == kMaskBf16 ? 0.f : bias[acc_channel(r, half)];
+
+  int64_t colno = pc.s0 / H;
+  int y = (int)(pc.s0 - colno * H);
+  if (CIN == 32) {
+    // rows y - 1, y, y + 1 of the wave's column: [column shift][channel half]
+    typedef bf16x8 RowFrags[3][2];
+    RowFrags ra, rb, rc;
+    int64_t img = 0;  // first pixel of the image
+    int px = 0;
+    auto load = [&](int yy, RowFrags& r) {
+      const bool row = yy >= 0 && yy < H;  // the same for the whole wave
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    const int64_t p = p0 + mb * 32 + col;
-    if (p >= P) continue;
+      for (int d = 0; d < 3; ++d) {
+        const bool in = row && (uint32_t)(px + d - 1) < (uint32_t)W;
+        const bf16* q = x + (img + (int64_t)yy * W + px + d - 1) * CIN + half * 8;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int c = 8 * g + 4 * half;
-      const float v0 = acc[mb][4 * g], v1 = acc[mb][4 * g + 1], v2 = acc[mb][4 * g + 2],
-                  v3 = acc[mb][4 * g + 3];
-      if (EPI == kBiasF32) {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + p * kCh + c) =
-            make_float4(v0, v1, v2, v3);
-      } else {
-        float r[4] = {v0, v1, v2, v3};
-        if (EPI == kReluBf16) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) r[i] = fmaxf(r[i], 0.0f);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) r[i] = bf(mask[p * kCh + c + i]) > 0.0f ? r[i] : 0.0f;
-        }
-        *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(out) + p * kCh + c) = pack4(r);
+        for (int h = 0; h < 2; ++h) r[d][h] = in ? *reinterpret_cast<const bf16x8*>(q + 16 * h) : zero8;
       }
+    };
+    // one row piece; the oldest row makes room for the next one as soon as
+    // its products are issued
+    auto step = [&](RowFrags& r0, RowFrags& r1, RowFrags& r2, bool more) {
+      floatx16 acc = start;
+#pragma unroll
+      for (int k = 0; k < 6; ++k)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[k], r0[k / 2][k & 1], acc, 0, 0, 0);
+      if (more) load(y + 2, r0);
+#pragma unroll
+      for (int k = 0; k < 6; ++k)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[6 % KSTEPS + k], r1[k / 2][k & 1], acc, 0, 0, 0);
+#pragma unroll
+      for (int k = 0; k < 6; ++k)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[12 % KSTEPS + k], r2[k / 2][k & 1], acc, 0, 0, 0);
+      if (px < W) conv_store<EPI>(acc, img + (int64_t)y * W + px, half, out, mask);
+      ++y;
+    };
+    for (int64_t s = pc.s0; s < pc.s1; ++colno, y = 0) {
+      const int64_t n = colno / pc.cols;
+      img = n * H * W;
+      px = (int)(colno - n * pc.cols) * kPiece + col;
+      const int rows = (int)(pc.s1 - s < H - y ? pc.s1 - s : H - y);
+      load(y - 1, ra);
+      load(y, rb);
+      load(y + 1, rc);
+      for (int r = 0; r < rows;) {
+        step(ra, rb, rc, r + 1 < rows);
+        if (++r == rows) break;
+        step(rb, rc, ra, r + 1 < rows);
+        if (++r == rows) break;
+        step(rc, ra, rb, r + 1 < rows);
+        ++r;
+      }
+      s += rows;
+    }
+  } else {
+    // 8 input channels: a K-step covers two taps, half a wave each
+    for (int64_t s = pc.s0; s < pc.s1; ++s, ++y) {
+      if (y == H) {
+        y = 0;
+        ++colno;
+      }
+      const int64_t n = colno / pc.cols, img = n * H * W;
+      const int px = (int)(colno - n * pc.cols) * kPiece + col;
+      bf16x8 a[KSTEPS];
+#pragma unroll
+      for (int k = 0; k < KSTEPS; ++k) {
+        const int tap = 2 * k + half, yy = y + tap / 3 - 1, xx = px + tap % 3 - 1;
+        const bool ok = tap < 9 && yy >= 0 && yy < H && xx >= 0 && xx < W;
+        a[k] = ok ? *reinterpret_cast<const bf16x8*>(x + (img + (int64_t)yy * W + xx) * CIN) : zero8;
+      }
+      floatx16 acc = start;
+#pragma unroll
+      for (int k = 0; k < KSTEPS; ++k)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[k], a[k], acc, 0, 0, 0);
+      if (px < W) conv_store<EPI>(acc, img + (int64_t)y * W + px, half, out, mask);
     }
   }
 }
@@ -853,10 +922,12 @@ fused_forward_kernel(
 
 // Training loss and its gradient with respect to o (bf16, 32 channels,
 // zeros beyond the 20 used): per low-resolution pixel, its four
-// full-resolution pixels. loss_sum[0] += the pixel's share.
+// full-resolution pixels. loss_part[workgroup]: its pixels' share (added in
+// a fixed order by update_kernel: an atomic per workgroup on one address
+// took most of this kernel's time).
 __global__ __launch_bounds__(256) void loss_kernel(const float* o, const bf16* x0,
                                                    const float4* target, int N, int H, int W,
-                                                   float err_weight, bf16* g, double* loss_sum) {
+                                                   float err_weight, bf16* g, double* loss_part) {
   const int64_t P = (int64_t)N * H * W;
   const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const double Pf = 4.0 * (double)P;  // full-resolution pixels
@@ -890,7 +961,10 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* o, const bf16* x
       gv[5 * s + 4] = (float)(2.0 / Pf) * err_weight * (z - e);
     }
 #pragma unroll
-    for (int c = 0; c < kCh; ++c) g[p * kCh + c] = (bf16)gv[c];
+    for (int c = 0; c < kCh; c += 4) {
+      const float r[4] = {gv[c], gv[c + 1], gv[c + 2], gv[c + 3]};
+      *reinterpret_cast<uint2*>(g + p * kCh + c) = pack4(r);
+    }
   }
   __shared__ double red[256];
   red[threadIdx.x] = part;
@@ -899,96 +973,296 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* o, const bf16* x
     if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0 && loss_sum) atomicAdd(loss_sum, red[0]);
+  if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0];
 }
 
-// Weight-gradient partial sums of one workgroup over its pixel chunk:
+// Weight-gradient partial sums of one workgroup (eight waves):
 // part[blk][t][ci][co] = sum_p x[p + off(t)][ci] g[p][co], and the bias
-// part[blk][9 CIN 32 + co] = sum_p g[p][co]. 32-pixel tiles are staged in
-// LDS (x gathered at the 9 taps, zero outside the image).
+// part[blk][9 CIN 32 + co] = sum_p g[p][co], on the matrix cores: K is the
+// pixels, 16 of an image row at a time, A = x (rows (tap,) ci), B = g (32
+// columns co), both bf16 as stored, FP32 accumulators. A lane's operand is 8
+// consecutive pixels of one channel, gathered with 2-byte loads (a wave's
+// load is two 64-byte runs).
+//  * 32 input channels: x stays in place and g is shifted instead, so a row
+//    of x meets the three rows of g around it at three column shifts: nine
+//    products for 8 + 10 loads per lane. The rows of g are kept while the
+//    wave walks down its column.
+//  * 8 input channels: the rows of A are (tap, ci), three tiles of 32, x
+//    shifted per lane.
+// Each wave keeps all its sums in registers (144 for 32 channels); the
+// waves' sums are folded through LDS in a fixed order. Bound by memory and
+// load latency: 128 bytes per pixel against 2 x 9 x 32 x 32 flop; 16 x 128 x
+// 128 pixels 37 us (32 channels; 466 as FP32 multiply-adds on the vector
+// units) and 42 us (8 channels; 161).
+constexpr int kWgWaves = 8;
+__device__ __forceinline__ uint32_t pair16(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
+__device__ __forceinline__ bf16x8 frag(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  return __builtin_bit_cast(bf16x8, make_uint4(a, b, c, d));
+}
+
+// Folds the waves' accumulators (T tiles of 32 x 32, register layout of the
+// product) and bias sums, and writes the workgroup's partial sums: rows
+// below `rows` of the T tiles, then the bias. LDS: 4 T tiles and the bias.
+template <int T>
+__device__ __forceinline__ void wgrad_out(floatx16 (&acc)[T], float bacc, int rows, float* lds,
+                                          float* out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float* sb = lds + 4 * T * 1024;  // [waves][64]
+  // a tile in LDS: 16-byte groups of four registers, lane by lane
+  auto at = [&](int w, int t, int g) {
+    return reinterpret_cast<float4*>(lds + ((w * T + t) * 4 + g) * 256 + lane * 4);
+  };
+  auto put = [&](int w) {
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *at(w, t, g) = make_float4(acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2],
+                                   acc[t][4 * g + 3]);
+  };
+  sb[wave * 64 + lane] = bacc;
+  if (wave >= 4) put(wave - 4);
+  __syncthreads();
+  if (wave < 4) {
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = *at(wave, t, g);
+        acc[t][4 * g] += v.x;
+        acc[t][4 * g + 1] += v.y;
+        acc[t][4 * g + 2] += v.z;
+        acc[t][4 * g + 3] += v.w;
+      }
+  }
+  __syncthreads();
+  if (wave < 4) put(wave);
+  __syncthreads();
+  // element (row, co) of the tiles: lane (row / 4 % 2) 32 + co, register
+  // 4 (row / 8 % 4) + row % 4 of tile row / 32
+  for (int e = threadIdx.x; e < rows * kCh; e += 64 * kWgWaves) {
+    const int row = e >> 5, co = e & 31, t = row >> 5, r = row & 31;
+    const int k = (t * 4 + (r >> 3)) * 256 + (((r >> 2) & 1) * 32 + co) * 4 + (r & 3);
+    out[e] = (lds[k] + lds[k + T * 1024]) + (lds[k + 2 * T * 1024] + lds[k + 3 * T * 1024]);
+  }
+  if (threadIdx.x < kCh) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWgWaves; ++w) v += sb[w * 64 + threadIdx.x] + sb[w * 64 + 32 + threadIdx.x];
+    out[rows * kCh + threadIdx.x] = v;
+  }
+}
+constexpr size_t wgrad_lds(int tiles) { return (size_t)(4 * tiles * 1024 + kWgWaves * 64) * 4; }
+
 template <int CIN>
-__global__ __launch_bounds__(256) void wgrad_kernel(const bf16* x, const bf16* g, int N, int H,
-                                                    int W, int64_t chunk, float* part) {
-  constexpr int PAIRS = CIN * kCh;           // (ci, co)
-  constexpr int PER = (PAIRS + 255) / 256;   // pairs per thread
-  __shared__ float sx[32][9][CIN];
-  __shared__ float sg[32][kCh];
-  const int64_t P = (int64_t)N * H * W;
-  const int64_t begin = (int64_t)blockIdx.x * chunk, end = min(P, begin + chunk);
-  float acc[PER][9];
+__global__ __launch_bounds__(64 * kWgWaves, 2) void wgrad_kernel(const bf16* __restrict__ xb,
+                                                              const bf16* __restrict__ gb, int N,
+                                                              int H, int W, float* part) {
+  extern __shared__ float wgrad_smem[];
+  constexpr int T = CIN == 32 ? 9 : 3;
+  const uint16_t* x = reinterpret_cast<const uint16_t*>(xb);
+  const uint16_t* g = reinterpret_cast<const uint16_t*>(gb);
+  const int lane = threadIdx.x & 63, ch = lane & 31, half = lane >> 5;
+  const Pieces pc = wave_pieces(N, H, W, 16);
+  floatx16 acc[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
   float bacc = 0.f;
+  int64_t colno = pc.s0 / H;
+  int y = (int)(pc.s0 - colno * H);
+  int64_t img = 0;
+  int x0 = 0;  // the lane's first pixel of the piece
+  if (CIN == 32) {
+    // per pixel x0 - 1 .. x0 + 8: element offset from the row, clamped into it
+    int off[10];
+    auto raw = [&](const uint16_t* p, int yy, int k) -> uint32_t {
+      const uint32_t v = p[(img + (int64_t)yy * W) * kCh + off[k]];
+      return (uint32_t)(x0 + k - 1) < (uint32_t)W ? v : 0u;
+    };
+    auto load_g = [&](int yy, uint32_t (&e)[10]) {
+      const bool row = yy >= 0 && yy < H;  // the same for the whole wave
 #pragma unroll
-  for (int k = 0; k < PER; ++k)
+      for (int k = 0; k < 10; ++k) e[k] = row ? raw(g, yy, k) : 0u;
+    };
+    // a row of g at the three shifts: [0] pixels x0 - 1 .. (dx = 1), [1] x0
+    // .., [2] x0 + 1 ..
+    typedef bf16x8 Shifts[3];
+    auto shifts = [&](const uint32_t (&e)[10], Shifts& s) {
 #pragma unroll
-    for (int t = 0; t < 9; ++t) acc[k][t] = 0.f;
-  for (int64_t t0 = begin; t0 < end; t0 += 32) {
-    const int cnt = (int)min<int64_t>(32, end - t0);
-    __syncthreads();
-    for (int i = threadIdx.x; i < 32 * 9 * CIN; i += 256) {
-      const int pi = i / (9 * CIN), rem = i - pi * 9 * CIN, t = rem / CIN, ci = rem - t * CIN;
-      float v = 0.f;
-      if (pi < cnt) {
-        const int64_t p = t0 + pi;
-        const int n = (int)(p / ((int64_t)H * W));
-        const int r = (int)(p - (int64_t)n * H * W), y = r / W + t / 3 - 1,
-                  xx = r % W + t % 3 - 1;
-        if (y >= 0 && y < H && xx >= 0 && xx < W)
-          v = bf(x[(((int64_t)n * H + y) * W + xx) * CIN + ci]);
+      for (int d = 0; d < 3; ++d)
+        s[d] = frag(pair16(e[d], e[d + 1]), pair16(e[d + 2], e[d + 3]), pair16(e[d + 4], e[d + 5]),
+                    pair16(e[d + 6], e[d + 7]));
+    };
+    Shifts ga, gm, gz;  // rows y - 1, y, y + 1
+    uint32_t ex[8], eg[10];
+    // one row of x against the rows g0, g1 and g2 (filled here from its
+    // loads); the next row's loads go out ahead of the products
+    auto step = [&](Shifts& g0, Shifts& g1, Shifts& g2, bool more) {
+      shifts(eg, g2);
+      const bf16x8 a = frag(pair16(ex[0], ex[1]), pair16(ex[2], ex[3]), pair16(ex[4], ex[5]),
+                            pair16(ex[6], ex[7]));
+      if (more) {
+        load_g(y + 2, eg);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) ex[k] = raw(x, y + 1, k + 1);
       }
-      sx[pi][t][ci] = v;
-    }
-    for (int i = threadIdx.x; i < 32 * kCh; i += 256) {
-      const int pi = i / kCh, co = i - pi * kCh;
-      sg[pi][co] = pi < cnt ? bf(g[(t0 + pi) * kCh + co]) : 0.f;
-    }
-    __syncthreads();
-    for (int pi = 0; pi < cnt; ++pi) {
+      // tap (dy, dx): x[y] meets g[y - dy] shifted by dx
 #pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        const int pair = threadIdx.x + 256 * k;
-        if (pair >= PAIRS) continue;
-        const int ci = pair / kCh, co = pair - ci * kCh;
-        const float gv = sg[pi][co];
-#pragma unroll
-        for (int t = 0; t < 9; ++t) acc[k][t] = fmaf(sx[pi][t][ci], gv, acc[k][t]);
+      for (int dx = -1; dx <= 1; ++dx) {
+        acc[dx + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g2[1 - dx], acc[dx + 1], 0, 0, 0);
+        acc[(dx + 4) % T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g1[1 - dx], acc[(dx + 4) % T], 0, 0, 0);
+        acc[(dx + 7) % T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g0[1 - dx], acc[(dx + 7) % T], 0, 0, 0);
       }
-      if (threadIdx.x < kCh) bacc += sg[pi][threadIdx.x];
+      const uint4 own = __builtin_bit_cast(uint4, g1[1]);  // the bias: row y, no shift
+      const uint32_t ow[4] = {own.x, own.y, own.z, own.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        bacc += __builtin_bit_cast(float, ow[k] << 16) +
+                __builtin_bit_cast(float, ow[k] & 0xFFFF0000u);
+      ++y;
+    };
+    for (int64_t s = pc.s0; s < pc.s1; ++colno, y = 0) {
+      const int64_t n = colno / pc.cols;
+      img = n * H * W;
+      x0 = (int)(colno - n * pc.cols) * 16 + 8 * half;
+      const int rows = (int)(pc.s1 - s < H - y ? pc.s1 - s : H - y);
+#pragma unroll
+      for (int k = 0; k < 10; ++k) off[k] = min(max(x0 + k - 1, 0), W - 1) * kCh + ch;
+      load_g(y - 1, eg);
+      shifts(eg, ga);
+      load_g(y, eg);
+      shifts(eg, gm);
+      load_g(y + 1, eg);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) ex[k] = raw(x, y, k + 1);
+      for (int r = 0; r < rows;) {
+        step(ga, gm, gz, r + 1 < rows);
+        if (++r == rows) break;
+        step(gm, gz, ga, r + 1 < rows);
+        if (++r == rows) break;
+        step(gz, ga, gm, r + 1 < rows);
+        ++r;
+      }
+      s += rows;
+    }
+  } else {
+    for (int64_t s = pc.s0; s < pc.s1; ++s, ++y) {
+      if (y == H) {
+        y = 0;
+        ++colno;
+      }
+      const int64_t n = colno / pc.cols;
+      img = n * H * W;
+      x0 = (int)(colno - n * pc.cols) * 16 + 8 * half;
+      uint32_t eb[8], ea[T][8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int px = x0 + k;
+        const uint32_t v = g[(img + (int64_t)y * W + min(px, W - 1)) * kCh + ch];
+        eb[k] = px < W ? v : 0u;
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const int tap = 4 * t + (ch >> 3), ci = ch & 7, yy = y + tap / 3 - 1, dx = tap % 3 - 1;
+        const bool row = tap < 9 && yy >= 0 && yy < H;
+        const int64_t base = (img + (int64_t)min(max(yy, 0), H - 1) * W) * CIN + ci;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int px = x0 + k + dx;
+          const uint32_t v = x[base + (int64_t)min(max(px, 0), W - 1) * CIN];
+          ea[t][k] = row && px >= 0 && px < W ? v : 0u;
+        }
+      }
+      const bf16x8 b = frag(pair16(eb[0], eb[1]), pair16(eb[2], eb[3]), pair16(eb[4], eb[5]),
+                            pair16(eb[6], eb[7]));
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            frag(pair16(ea[t][0], ea[t][1]), pair16(ea[t][2], ea[t][3]),
+                 pair16(ea[t][4], ea[t][5]), pair16(ea[t][6], ea[t][7])),
+            b, acc[t], 0, 0, 0);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) bacc += __builtin_bit_cast(float, eb[k] << 16);
     }
   }
-  float* out = part + (int64_t)blockIdx.x * (9 * PAIRS + kCh);
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int pair = threadIdx.x + 256 * k;
-    if (pair >= PAIRS) continue;
-    const int ci = pair / kCh, co = pair - ci * kCh;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) out[((int64_t)t * CIN + ci) * kCh + co] = acc[k][t];
-  }
-  if (threadIdx.x < kCh) out[9 * PAIRS + threadIdx.x] = bacc;
+  wgrad_out<T>(acc, bacc, 9 * CIN, wgrad_smem, part + (int64_t)blockIdx.x * (9 * CIN * kCh + kCh));
 }
 
-// grads[i] = sum over blocks (in order) of part[blk][i]
-__global__ void reduce_kernel(const float* part, int blocks, int64_t n, float* grads) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    float s = 0.f;
-    for (int b = 0; b < blocks; ++b) s += part[(int64_t)b * n + i];
-    grads[i] = s;
+// The parameters' update from the layers' partial sums, in one launch:
+// workgroup b < 64-parameter groups: grads[i] = sum over the layer's
+// workgroups of part[blk][i], four runs of them at a time, the runs then
+// added in order (deterministic); with adam set one Adam step on the FP32
+// master weight and its bf16 copies in the GEMM layouts (see pack_kernel).
+// The last workgroup adds the loss kernel's partial sums in a fixed order.
+// 7 us for 256 workgroups a layer (478 in four launches with one thread per
+// parameter walking 512 partial sums, and four more to pack the weights).
+struct UpdateArgs {
+  const float* part[kLayers];
+  int32_t blocks[kLayers];
+  float *w, *g, *m, *v;
+  bf16 *fw[kLayers], *bw[kLayers];
+  const double* loss_part;
+  int32_t loss_n;
+  double* loss;
+  float lr, c1, c2;
+  int32_t adam;  // 0: gradients only
+};
+constexpr int kUpdateGroups = (int)((kParams + 63) / 64);
+__global__ __launch_bounds__(256) void update_kernel(UpdateArgs a) {
+  __shared__ double red[256];
+  if (blockIdx.x == kUpdateGroups) {
+    double s = 0.0;
+    for (int i = threadIdx.x; i < a.loss_n; i += 256) s += a.loss_part[i];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int k = 128; k > 0; k >>= 1) {
+      if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) *a.loss = red[0];
+    return;
   }
-}
-
-// Adam on the FP32 master weights.
-__global__ void adam_kernel(float* w, const float* g, float* m, float* v, int64_t n, float lr,
-                            float c1, float c2) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = 0.9f * m[i] + 0.1f * gi;
-    const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + 1e-8f);
+  float* runs = reinterpret_cast<float*>(red);
+  const int col = threadIdx.x & 63, run = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + col;
+  int layer = 0;
+  int64_t first = 0;
+#pragma unroll
+  for (int l = 0; l + 1 < kLayers; ++l)
+    if (layer == l && i - first >= layer_size(l)) {
+      first += layer_size(l);
+      layer = l + 1;
+    }
+  const int64_t k = i - first, n = layer_size(layer);
+  float s = 0.f;
+  if (i < kParams) {
+    const int blocks = a.blocks[layer], per = (blocks + 3) / 4;
+    const float* p = a.part[layer] + k;
+    const int b1 = min(blocks, (run + 1) * per);
+#pragma unroll 8
+    for (int b = run * per; b < b1; ++b) s += p[(int64_t)b * n];
   }
+  runs[run * 64 + col] = s;
+  __syncthreads();
+  if (run != 0 || i >= kParams) return;
+  const float gi = (runs[col] + runs[64 + col]) + (runs[128 + col] + runs[192 + col]);
+  a.g[i] = gi;
+  if (!a.adam) return;
+  const float mi = 0.9f * a.m[i] + 0.1f * gi;
+  const float vi = 0.999f * a.v[i] + 0.001f * gi * gi;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float w = a.w[i] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + 1e-8f);
+  a.w[i] = w;
+  const int cin = layer == 0 ? 8 : kCh;
+  if (k >= (int64_t)9 * cin * kCh) return;  // a bias
+  const int co = (int)(k & 31), kk = (int)(k >> 5);  // kk = tap cin + ci
+  a.fw[layer][((int64_t)(kk >> 3) * kCh + co) * 8 + (kk & 7)] = (bf16)w;
+  if (layer == 0) return;
+  const int tap = kk >> 5, ci = kk & 31, kb = (8 - tap) * kCh + co;
+  a.bw[layer][((int64_t)(kb >> 3) * kCh + ci) * 8 + (kb & 7)] = (bf16)w;
 }
 
 // Pack one layer's FP32 weights w[9][cin][32] into the GEMM layouts:
@@ -1032,7 +1306,7 @@ struct sg_upsampler {
   float* o = nullptr;
   bf16* ga = nullptr;       // gradient buffers
   bf16* gb = nullptr;
-  float* part = nullptr;    // weight-gradient partial sums
+  float* part[kLayers] = {};  // weight-gradient partial sums [part_blocks][layer_size]
   int part_blocks = 0;
   double* acc = nullptr;    // device doubles: loss, partials or sums, per-image results
   int64_t acc_n = 0;
@@ -1045,11 +1319,12 @@ struct sg_upsampler {
 namespace {
 
 void up_free(sg_upsampler* u) {
-  void* ptrs[] = {u->params, u->grads, u->m,    u->v,   u->x0, u->o,
-                  u->ga,     u->gb,    u->part, u->acc, u->tl, u->mask};
+  void* ptrs[] = {u->params, u->grads, u->m,   u->v,  u->x0,  u->o,
+                  u->ga,     u->gb,    u->acc, u->tl, u->mask};
   for (void* p : ptrs)
     if (p) hipFree(p);
   for (int l = 0; l < kLayers; ++l) {
+    if (u->part[l]) hipFree(u->part[l]);
     if (u->fw[l]) hipFree(u->fw[l]);
     if (u->bw[l]) hipFree(u->bw[l]);
   }
@@ -1076,9 +1351,12 @@ sg_status pack_weights(sg_upsampler* u, hipStream_t s) {
 template <int CIN, int EPI>
 sg_status conv(const bf16* x, int N, int H, int W, const bf16* wt, const float* bias, void* out,
                const bf16* mask, hipStream_t s) {
-  const int64_t waves = ((int64_t)N * H * W + 63) / 64;
-  hipLaunchKernelGGL((conv_kernel<CIN, EPI>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s,
-                     x, N, H, W, reinterpret_cast<const bf16x8*>(wt), bias, out, mask);
+  // two workgroups of four waves per CU, each wave a run of row pieces (at
+  // least two, so that rows are shared)
+  const int64_t pieces = (int64_t)N * ((W + kPiece - 1) / kPiece) * H;
+  const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(512, (pieces + 7) / 8));
+  hipLaunchKernelGGL((conv_kernel<CIN, EPI>), dim3((unsigned)groups), dim3(256), 0, s, x, N, H, W,
+                     reinterpret_cast<const bf16x8*>(wt), bias, out, mask);
   SG_HIP(hipGetLastError());
   return SG_OK;
 }
@@ -1114,42 +1392,66 @@ sg_status forward(sg_upsampler* u, int n, int h, int w, const float* rgba, const
                             nullptr, s);
 }
 
+// Partial sums of a layer's weight gradients; *blocks receives how many.
 template <int CIN>
 sg_status wgrad(sg_upsampler* u, const bf16* x, const bf16* g, int n, int h, int w, int layer,
-                hipStream_t s) {
-  const int64_t P = (int64_t)n * h * w;
-  const int blocks = (int)std::min<int64_t>(u->part_blocks, (P + 63) / 64);
-  const int64_t chunk = (((P + blocks - 1) / blocks + 63) / 64) * 64;
-  const int used = (int)((P + chunk - 1) / chunk);
-  hipLaunchKernelGGL(wgrad_kernel<CIN>, dim3(used), dim3(256), 0, s, x, g, n, h, w, chunk,
-                     u->part);
-  const int64_t nn = layer_size(layer);
-  hipLaunchKernelGGL(reduce_kernel, dim3(blocks_of(nn)), dim3(256), 0, s, u->part, used, nn,
-                     u->grads + layer_off(layer));
+                int32_t* blocks, hipStream_t s) {
+  // one workgroup of eight waves per CU, at least two row pieces per wave
+  const int64_t pieces = (int64_t)n * ((w + 15) / 16) * h;
+  const int groups = (int)std::max<int64_t>(
+      1, std::min<int64_t>(u->part_blocks, (pieces + 2 * kWgWaves - 1) / (2 * kWgWaves)));
+  constexpr size_t lds = wgrad_lds(CIN == 32 ? 9 : 3);
+  SG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_kernel<CIN>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(wgrad_kernel<CIN>, dim3(groups), dim3(64 * kWgWaves), lds, s, x, g, n, h, w,
+                     u->part[layer]);
   SG_HIP(hipGetLastError());
+  *blocks = groups;
   return SG_OK;
 }
 
+// Gradients of one batch into u->grads and its loss into acc[0]; with adam
+// set also the Adam step.
 sg_status gradients(sg_upsampler* u, int n, int h, int w, const float* rgba, const float* depth,
-                    double depth_scale, const float* target, double err_weight, hipStream_t s) {
+                    double depth_scale, const float* target, double err_weight, bool adam, float lr,
+                    float c1, float c2, hipStream_t s) {
   sg_status st = forward(u, n, h, w, rgba, depth, depth_scale, s);
   if (st != SG_OK) return st;
   const int64_t P = (int64_t)n * h * w;
-  SG_HIP(hipMemsetAsync(u->acc, 0, sizeof(double), s));
-  hipLaunchKernelGGL(loss_kernel, dim3(blocks_of(P)), dim3(256), 0, s, u->o, u->x0,
+  UpdateArgs a{};
+  a.loss = u->acc;
+  a.loss_part = u->acc + 1;  // one per 256 pixels: fewer than max_pixels
+  a.loss_n = (int32_t)((P + 255) / 256);
+  hipLaunchKernelGGL(loss_kernel, dim3((unsigned)a.loss_n), dim3(256), 0, s, u->o, u->x0,
                      reinterpret_cast<const float4*>(target), n, h, w, (float)err_weight, u->ga,
-                     u->acc);
+                     u->acc + 1);
   SG_HIP(hipGetLastError());
   // layer 4 (input h3), then back through the ReLUs
   bf16* g = u->ga;
   bf16* gn = u->gb;
   for (int l = 3; l >= 1; --l) {
-    if ((st = wgrad<32>(u, u->h[l - 1], g, n, h, w, l, s)) != SG_OK) return st;
+    if ((st = wgrad<32>(u, u->h[l - 1], g, n, h, w, l, &a.blocks[l], s)) != SG_OK) return st;
     if ((st = conv<32, kMaskBf16>(g, n, h, w, u->bw[l], nullptr, gn, u->h[l - 1], s)) != SG_OK)
       return st;
     std::swap(g, gn);
   }
-  return wgrad<8>(u, u->x0, g, n, h, w, 0, s);
+  if ((st = wgrad<8>(u, u->x0, g, n, h, w, 0, &a.blocks[0], s)) != SG_OK) return st;
+  for (int l = 0; l < kLayers; ++l) {
+    a.part[l] = u->part[l];
+    a.fw[l] = u->fw[l];
+    a.bw[l] = u->bw[l];
+  }
+  a.w = u->params;
+  a.g = u->grads;
+  a.m = u->m;
+  a.v = u->v;
+  a.adam = adam ? 1 : 0;
+  a.lr = lr;
+  a.c1 = c1;
+  a.c2 = c2;
+  hipLaunchKernelGGL(update_kernel, dim3(kUpdateGroups + 1), dim3(256), 0, s, a);
+  SG_HIP(hipGetLastError());
+  return SG_OK;
 }
 
 // Inference into out_rgba / out_err; with sums, the per-image sums of the
@@ -1242,7 +1544,7 @@ sg_status sg_up_create(int32_t device, int64_t max_pixels, sg_upsampler** out) {
   sg_upsampler* u = new sg_upsampler;
   u->device = device;
   u->max_pixels = max_pixels;
-  u->part_blocks = 512;
+  u->part_blocks = 256;
   // loss, partials or sums [max_pixels] (a tile holds at least one pixel),
   // results [max_pixels]
   u->acc_n = 2 + 2 * max_pixels;
@@ -1263,7 +1565,8 @@ sg_status sg_up_create(int32_t device, int64_t max_pixels, sg_upsampler** out) {
   al((void**)&u->o, max_pixels * kCh * 4);
   al((void**)&u->ga, max_pixels * kCh * 2);
   al((void**)&u->gb, max_pixels * kCh * 2);
-  al((void**)&u->part, (int64_t)u->part_blocks * (9 * 32 * kCh + kCh) * 4);
+  for (int l = 0; l < kLayers; ++l)
+    al((void**)&u->part[l], (int64_t)u->part_blocks * layer_size(l) * 4);
   al((void**)&u->acc, u->acc_n * 8);
   al((void**)&u->tl, (4 + max_pixels) * 4);
   al((void**)&u->mask, max_pixels);
@@ -1343,9 +1646,12 @@ sg_status sg_up_forward_flag(sg_upsampler* up, int32_t n, int32_t h, int32_t w,
                threshold_db, (hipStream_t)hip_stream);
 }
 
-sg_status sg_up_gradients(sg_upsampler* up, int32_t n, int32_t h, int32_t w, const float* rgba,
-                          const float* depth, double depth_scale, const float* target,
-                          double err_weight, float* grads, double* loss, void* hip_stream) {
+// Both training entry points: the gradients of one batch, and with lr > 0
+// the Adam step on them.
+static sg_status train(sg_upsampler* up, int32_t n, int32_t h, int32_t w, const float* rgba,
+                       const float* depth, double depth_scale, const float* target,
+                       double err_weight, double lr, float* grads, double* loss,
+                       void* hip_stream) {
   sg_status st = check_batch(up, n, h, w, rgba, depth);
   if (st != SG_OK) return st;
   if (!target || !(std::isfinite(depth_scale) && depth_scale > 0.0) || !std::isfinite(err_weight))
@@ -1353,30 +1659,35 @@ sg_status sg_up_gradients(sg_upsampler* up, int32_t n, int32_t h, int32_t w, con
   DeviceGuard guard(up->device);
   if (!guard.ok) return fail(SG_ERR_DEVICE, "cannot select device");
   hipStream_t s = (hipStream_t)hip_stream;
-  if ((st = gradients(up, n, h, w, rgba, depth, depth_scale, target, err_weight, s)) != SG_OK)
+  float c1 = 1.f, c2 = 1.f;
+  if (lr > 0.0) {
+    const double step = (double)(up->step + 1);
+    c1 = (float)(1.0 / (1.0 - std::pow(0.9, step)));
+    c2 = (float)(1.0 / (1.0 - std::pow(0.999, step)));
+  }
+  if ((st = gradients(up, n, h, w, rgba, depth, depth_scale, target, err_weight, lr > 0.0,
+                      (float)lr, c1, c2, s)) != SG_OK)
     return st;
+  if (lr > 0.0) up->step += 1;
   if (grads) SG_HIP(hipMemcpyAsync(grads, up->grads, kParams * 4, hipMemcpyDeviceToHost, s));
   if (loss) SG_HIP(hipMemcpyAsync(loss, up->acc, sizeof(double), hipMemcpyDeviceToHost, s));
   if (grads || loss) SG_HIP(hipStreamSynchronize(s));
   return SG_OK;
 }
 
+sg_status sg_up_gradients(sg_upsampler* up, int32_t n, int32_t h, int32_t w, const float* rgba,
+                          const float* depth, double depth_scale, const float* target,
+                          double err_weight, float* grads, double* loss, void* hip_stream) {
+  return train(up, n, h, w, rgba, depth, depth_scale, target, err_weight, 0.0, grads, loss,
+               hip_stream);
+}
+
 sg_status sg_up_train_step(sg_upsampler* up, int32_t n, int32_t h, int32_t w, const float* rgba,
                            const float* depth, double depth_scale, const float* target,
                            double err_weight, double lr, double* loss, void* hip_stream) {
   if (!(std::isfinite(lr) && lr > 0.0)) return fail(SG_ERR_INVALID_ARG, "sg_up_train_step: lr");
-  sg_status st = sg_up_gradients(up, n, h, w, rgba, depth, depth_scale, target, err_weight,
-                                 nullptr, loss, hip_stream);
-  if (st != SG_OK) return st;
-  DeviceGuard guard(up->device);
-  hipStream_t s = (hipStream_t)hip_stream;
-  up->step += 1;
-  const float c1 = (float)(1.0 / (1.0 - std::pow(0.9, (double)up->step)));
-  const float c2 = (float)(1.0 / (1.0 - std::pow(0.999, (double)up->step)));
-  hipLaunchKernelGGL(adam_kernel, dim3(blocks_of(kParams)), dim3(256), 0, s, up->params,
-                     up->grads, up->m, up->v, kParams, (float)lr, c1, c2);
-  SG_HIP(hipGetLastError());
-  return pack_weights(up, s);
+  return train(up, n, h, w, rgba, depth, depth_scale, target, err_weight, lr, nullptr, loss,
+               hip_stream);
 }
 
 sg_status sg_up_set_fused(sg_upsampler* up, int32_t fused) {
