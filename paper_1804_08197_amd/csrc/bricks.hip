@@ -8,9 +8,9 @@
 // fastest, indexed [z][y][x]; they need no volume handle and run on the
 // current device.
 #include <algorithm>
-#include <vector>
+#include <type_traits>
 
-#include "sg_internal.h"
+#include "brick_rows.h"
 
 namespace sg {
 
@@ -23,47 +23,163 @@ struct Dims {
 // One coarser level: voxel g = (sum of the 2x2x2 children 2g + delta, each
 // child index clamped to the finer level, + 4) >> 3 (the pyramid rule of
 // the resident volume's builder, on a linear array).
+//
+// Rows of dst are dealt to the workgroups in windows of `rows`; a thread
+// makes two voxels of a row (`half` = ceil(dst x / 2) of them to a row) from
+// four voxels of each of four source rows, one load a row where the four lie
+// in the level at an address aligned to them, else voxel by voxel. Bound by
+// reading the source once: three levels of 700x512x420 uint16 122 us.
 template <typename T>
-__global__ void pyramid_level_kernel(const T* src, Dims s, T* dst, Dims d, int64_t total) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t x = i % d.n[0];
-    const int64_t y = (i / d.n[0]) % d.n[1];
-    const int64_t z = i / (d.n[0] * d.n[1]);
-    const int64_t x0 = 2 * x, x1 = min(2 * x + 1, s.n[0] - 1);
-    const int64_t y0 = 2 * y, y1 = min(2 * y + 1, s.n[1] - 1);
-    const int64_t z0 = 2 * z, z1 = min(2 * z + 1, s.n[2] - 1);
-    const int64_t sy = s.n[0], sz = s.n[0] * s.n[1];
-    uint32_t sum = (uint32_t)src[z0 * sz + y0 * sy + x0] + (uint32_t)src[z0 * sz + y0 * sy + x1] +
-                   (uint32_t)src[z0 * sz + y1 * sy + x0] + (uint32_t)src[z0 * sz + y1 * sy + x1] +
-                   (uint32_t)src[z1 * sz + y0 * sy + x0] + (uint32_t)src[z1 * sz + y0 * sy + x1] +
-                   (uint32_t)src[z1 * sz + y1 * sy + x0] + (uint32_t)src[z1 * sz + y1 * sy + x1];
-    dst[i] = (T)((sum + 4u) >> 3);
+__device__ __forceinline__ void four_voxels(const T* row, int64_t x, int64_t n, uint32_t (&v)[4]) {
+  const T* p = row + x;
+  if (x + 4 <= n && (reinterpret_cast<uintptr_t>(p) & (4 * sizeof(T) - 1)) == 0) {
+    if (sizeof(T) == 1) {
+      const uint32_t a = *reinterpret_cast<const uint32_t*>(p);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = (a >> (8 * k)) & 0xFFu;
+    } else {
+      const uint2 a = *reinterpret_cast<const uint2*>(p);
+      v[0] = a.x & 0xFFFFu;
+      v[1] = a.x >> 16;
+      v[2] = a.y & 0xFFFFu;
+      v[3] = a.y >> 16;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = row[min(x + k, n - 1)];
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void pyramid_level_kernel(const T* __restrict__ src, Dims s,
+                                                            T* __restrict__ dst, Dims d, int rows,
+                                                            int half) {
+  const int64_t r0 = (int64_t)blockIdx.x * rows, all = d.n[1] * d.n[2];
+  const int here = (int)min((int64_t)rows, all - r0);
+  const float inv_h = __builtin_amdgcn_rcpf((float)half);
+  for (int i = threadIdx.x; i < here * half; i += 256) {
+    const int dr = quot_exact(i, inv_h);
+    const int64_t row = r0 + dr, x = 2 * (int64_t)(i - dr * half);
+    const int64_t z = row / d.n[1], y = row - z * d.n[1];
+    const int64_t y1 = min(2 * y + 1, s.n[1] - 1), z1 = min(2 * z + 1, s.n[2] - 1);
+    const T *a = src + (2 * z * s.n[1] + 2 * y) * s.n[0], *b = src + (2 * z * s.n[1] + y1) * s.n[0],
+            *c = src + (z1 * s.n[1] + 2 * y) * s.n[0], *e = src + (z1 * s.n[1] + y1) * s.n[0];
+    uint32_t va[4], vb[4], vc[4], ve[4];
+    four_voxels(a, 2 * x, s.n[0], va);
+    four_voxels(b, 2 * x, s.n[0], vb);
+    four_voxels(c, 2 * x, s.n[0], vc);
+    four_voxels(e, 2 * x, s.n[0], ve);
+    uint32_t o[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      o[k] = (va[2 * k] + va[2 * k + 1] + vb[2 * k] + vb[2 * k + 1] + vc[2 * k] + vc[2 * k + 1] +
+              ve[2 * k] + ve[2 * k + 1] + 4u) >> 3;
+    T* q = dst + row * d.n[0] + x;
+    if (sizeof(T) == 2 && x + 1 < d.n[0] && (reinterpret_cast<uintptr_t>(q) & 3) == 0) {
+      *reinterpret_cast<uint32_t*>(q) = o[0] | (o[1] << 16);
+    } else {
+      q[0] = (T)o[0];
+      if (x + 1 < d.n[0]) q[1] = (T)o[1];
+    }
   }
 }
 
 // Brick regions: region j holds level voxels B b_j - 1 .. B b_j + B per
 // axis, indices clamped to the level, as an S^3 block (S = B + 2), x
-// fastest. One thread per region voxel.
-template <typename T>
-__global__ void region_kernel(const T* level, Dims d, const int32_t* coords, int32_t B,
-                              T* out, int64_t total) {
-  const int64_t S = B + 2, S3 = S * S * S;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = i / S3;
-    const int64_t r = i - j * S3;
-    const int64_t lx = r % S, ly = (r / S) % S, lz = r / (S * S);
-    const int32_t* c = coords + 3 * j;
-    const int64_t gx = min(max((int64_t)B * c[0] - 1 + lx, (int64_t)0), d.n[0] - 1);
-    const int64_t gy = min(max((int64_t)B * c[1] - 1 + ly, (int64_t)0), d.n[1] - 1);
-    const int64_t gz = min(max((int64_t)B * c[2] - 1 + lz, (int64_t)0), d.n[2] - 1);
-    out[i] = level[(gz * d.n[1] + gy) * d.n[0] + gx];
-  }
-}
+// fastest. The brick coordinates of a launch travel in its arguments (three
+// 21-bit fields each): no copy and no wait.
+//
+// A brick's S x S rows are shared by `per` workgroups in windows; a thread
+// makes four voxels of a row (the last of a row may be two: S is even) with
+// one load and one store, at whatever address the row starts (the compiler
+// picks the instructions from the types' alignment), kQuads of them in
+// flight; at the level's ends in x it reads voxel by voxel. SMALL: the S
+// planes a brick spans hold fewer than 2^31 voxels and S n_y < 2^24, so a
+// row's offset from the brick's first plane is 32-bit arithmetic with 24-bit
+// products (beside one scalar base); otherwise 64-bit.
+//
+// Bound by memory. A row of 66 uint16 voxels is 132 bytes at an odd voxel,
+// so it pulls two or three 128-byte lines, which its neighbours in x need
+// too, so neighbouring bricks go to one XCD and its L2. 812 bricks of 64^3
+// uint16 (five launches): 266 us (740 with one thread and two 64-bit
+// divisions per voxel, plus a copy of the coordinates and a wait per call);
+// two voxels or eight to a thread ran at 272 and 410 us (a row of 66 leaves
+// an eight mostly outside).
+constexpr int kLaunchBricks = 448;  // 3.5 KiB of arguments
+struct BrickList {
+  uint64_t b[kLaunchBricks];
+};
+constexpr int kQuads = 4;
 
-int grid_for(int64_t work) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>((work + 255) / 256, 65536));
+template <typename T, bool SMALL>
+__global__ __launch_bounds__(256) void region_kernel(const T* __restrict__ level, Dims d,
+                                                     BrickList list, int n, int B, int per,
+                                                     T* __restrict__ out) {
+  // (any alignment: the compiler picks the load from it)
+  typedef T Quad __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  // workgroup w runs on XCD w % 8: the same rows of eight consecutive bricks
+  // (neighbours in x, as a rule) are taken by one XCD in turn
+  const int turn = (int)(blockIdx.x >> 3), unit = (turn >> 3) * 8 + (int)(blockIdx.x & 7);
+  const int j = (unit / per) * 8 + (turn & 7), part = unit % per;
+  if (j >= n) return;
+  const int S = B + 2, quads = (S + 3) / 4, rows = S * S;
+  const uint64_t packed = list.b[j];
+  // stored voxel (0, 0, 0) of the brick (coordinates below 2^20, see check_dims)
+  const int g0 = B * (int)(packed & 0x1FFFFF) - 1, g1 = B * (int)((packed >> 21) & 0x1FFFFF) - 1,
+            g2 = B * (int)(packed >> 42) - 1;
+  const int n0 = (int)d.n[0], n1 = (int)d.n[1], n2 = (int)d.n[2];
+  const int zb = max(g2, 0);  // (a brick's core starts inside the level)
+  const T* base = level + (int64_t)zb * n1 * n0;
+  out += (int64_t)j * rows * S;
+  const int chunk = (rows + per - 1) / per, first = part * chunk, last = min(rows, first + chunk);
+  // (a window's items and a brick's rows stay below 2^21, see quot_exact)
+  const int window = (1 << 20) / quads;
+  const float inv_q = __builtin_amdgcn_rcpf((float)quads), inv_s = __builtin_amdgcn_rcpf((float)S);
+  for (int r0 = first; r0 < last; r0 += window) {
+    const int items = min(window, last - r0) * quads;
+    for (int i0 = threadIdx.x; i0 < items; i0 += 256 * kQuads) {
+      uint32_t v[kQuads][4];
+      int at[kQuads];
+      bool two[kQuads];
+#pragma unroll
+      for (int u = 0; u < kQuads; ++u) {
+        const int i = min(i0 + 256 * u, items - 1);
+        const int dr = quot_exact(i, inv_q), r = r0 + dr, x = 4 * (i - dr * quads);
+        const int z = quot_exact(r, inv_s), y = r - z * S;
+        const int gy = min(max(g1 + y, 0), n1 - 1), gz = min(max(g2 + z, 0), n2 - 1) - zb;
+        at[u] = r * S + x;
+        two[u] = x + 2 >= S;
+        const T* row;
+        if (SMALL)
+          row = base + __umul24(__umul24(gz, n1) + gy, n0);
+        else
+          row = base + ((int64_t)gz * n1 + gy) * n0;
+        const int gx = g0 + x;
+        if (gx >= 0 && gx + 4 <= n0) {
+          const Quad q = *reinterpret_cast<const Quad*>(row + gx);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[u][k] = q[k];
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[u][k] = row[min(max(gx + k, 0), n0 - 1)];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kQuads; ++u) {
+        if (i0 + 256 * u >= items) break;
+        T* o = out + at[u];
+        if (!two[u]) {
+          Quad q;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) q[k] = (T)v[u][k];
+          *reinterpret_cast<Quad*>(o) = q;
+        } else {
+          o[0] = (T)v[u][0];
+          o[1] = (T)v[u][1];
+        }
+      }
+    }
+  }
 }
 
 // Select the caller's current device explicitly for this thread, as every
@@ -112,11 +228,14 @@ extern "C" sg_status sg_pyramid_level(int32_t dtype, const int32_t src_dims[3], 
   // hold an earlier call's error)
   const void* sp = src;
   void* dp = dst;
-  int64_t tot = total;
-  void* pa[] = {&sp, &s, &dp, &d, &tot};
+  // windows of about 2048 voxel pairs (eight per thread)
+  int half = (int)((d.n[0] + 1) / 2);
+  int rows = std::max(1, 2048 / half);
+  void* pa[] = {&sp, &s, &dp, &d, &rows, &half};
+  const int64_t groups = (d.n[1] * d.n[2] + rows - 1) / rows;
   const void* k = dtype == SG_U8 ? reinterpret_cast<const void*>(pyramid_level_kernel<uint8_t>)
                                  : reinterpret_cast<const void*>(pyramid_level_kernel<uint16_t>);
-  SG_HIP(hipLaunchKernel(k, dim3(grid_for(total)), dim3(256), pa, 0, (hipStream_t)hip_stream));
+  SG_HIP(hipLaunchKernel(k, dim3((unsigned)groups), dim3(256), pa, 0, (hipStream_t)hip_stream));
   return SG_OK;
 }
 
@@ -142,23 +261,31 @@ extern "C" sg_status sg_brick_regions(int32_t dtype, const int32_t dims[3], cons
   Dims d;
   for (int a = 0; a < 3; ++a) d.n[a] = dims[a];
   const int64_t S = brick + 2;
-  const int64_t total = (int64_t)n * S * S * S;
   int dev = 0;
   if ((st = current_device(&dev)) != SG_OK) return st;
-  hipStream_t str = (hipStream_t)hip_stream;
-  int32_t* dc = nullptr;
-  const size_t cbytes = (size_t)n * 3 * sizeof(int32_t);
-  SG_HIP(hipMallocAsync((void**)&dc, cbytes, str));
-  SG_HIP(hipMemcpyAsync(dc, coords, cbytes, hipMemcpyHostToDevice, str));
-  // the host coordinates are consumed before the call returns
-  SG_HIP(hipStreamSynchronize(str));
+  const int64_t bpv = dtype == SG_U8 ? 1 : 2;
   const void* lvl = level;
-  int64_t tot = total;
-  void* pa[] = {&lvl, &d, &dc, &brick, &out, &tot};
-  const void* k = dtype == SG_U8 ? reinterpret_cast<const void*>(region_kernel<uint8_t>)
-                                 : reinterpret_cast<const void*>(region_kernel<uint16_t>);
-  const hipError_t le = hipLaunchKernel(k, dim3(grid_for(total)), dim3(256), pa, 0, str);
-  SG_HIP(hipFreeAsync(dc, str));
-  if (le != hipSuccess) return hip_fail(le, "region_kernel launch");
+  const bool small = S * d.n[1] < (1 << 24) && S * d.n[0] * d.n[1] < ((int64_t)1 << 31) &&
+                     d.n[0] < (1 << 24);
+  const void* k =
+      dtype == SG_U8 ? (small ? reinterpret_cast<const void*>(region_kernel<uint8_t, true>)
+                              : reinterpret_cast<const void*>(region_kernel<uint8_t, false>))
+                     : (small ? reinterpret_cast<const void*>(region_kernel<uint16_t, true>)
+                              : reinterpret_cast<const void*>(region_kernel<uint16_t, false>));
+  BrickList list;
+  for (int32_t i0 = 0; i0 < n; i0 += kLaunchBricks) {
+    const int m = std::min<int32_t>(kLaunchBricks, n - i0);
+    for (int i = 0; i < m; ++i) {
+      const int32_t* c = coords + 3 * (int64_t)(i0 + i);
+      list.b[i] = (uint64_t)c[0] | ((uint64_t)c[1] << 21) | ((uint64_t)c[2] << 42);
+    }
+    int per = groups_per_brick(m, (int)(S * S * ((S + 3) / 4) * kRowBatch / kQuads));
+    int nb = m;
+    const int64_t units = (int64_t)((m + 7) / 8) * per;  // dealt to the XCDs in turn
+    void* o = static_cast<uint8_t*>(out) + (int64_t)i0 * S * S * S * bpv;
+    void* pa[] = {&lvl, &d, &list, &nb, &brick, &per, &o};
+    SG_HIP(hipLaunchKernel(k, dim3((unsigned)((units + 7) / 8 * 64)), dim3(256), pa, 0,
+                           (hipStream_t)hip_stream));
+  }
   return SG_OK;
 }
