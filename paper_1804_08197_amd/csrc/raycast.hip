@@ -70,9 +70,17 @@ LaunchConfig effective_config(const Volume* v, const sg_render_params* p) {
 // log2 waves per workgroup: one wave per wave tile, at most four
 int wg_log_of(const LaunchConfig& c) { return std::min(2, 2 * c.tile_log); }
 
+size_t staging_bytes(const LaunchConfig& c) {
+  return c.gather ? 0 : ((size_t)1 << wg_log_of(c)) * (size_t)c.stage_bytes;
+}
 size_t lds_bytes(const Volume* v, const LaunchConfig& c) {
-  size_t tf = (size_t)v->d.channels * v->tf_n * 32;  // value and difference per entry
-  return c.gather ? tf : tf + ((size_t)1 << wg_log_of(c)) * (size_t)c.stage_bytes;
+  return (size_t)tf_lds_entries(v->d.channels, v->tf_n) * 16 + staging_bytes(c);
+}
+// What a configuration is checked against: value and difference per entry,
+// whatever the kernel keeps (which configurations are accepted does not
+// depend on it).
+size_t lds_budget(const Volume* v, const LaunchConfig& c) {
+  return (size_t)v->d.channels * v->tf_n * 32 + staging_bytes(c);
 }
 
 sg_status check_config(const Volume* v, const LaunchConfig& c) {
@@ -81,7 +89,7 @@ sg_status check_config(const Volume* v, const LaunchConfig& c) {
       c.bt_log < c.tile_log || c.stage_bytes < 1024 || c.stage_bytes > 32768 ||
       c.stage_bytes % 16 != 0)
     return fail(SG_ERR_INVALID_ARG, "launch configuration out of range");
-  if (v && lds_bytes(v, c) > 160 * 1024)
+  if (v && lds_budget(v, c) > 160 * 1024)
     return fail(SG_ERR_UNSUPPORTED, "launch configuration exceeds the LDS budget");
   return SG_OK;
 }
@@ -635,7 +643,7 @@ extern "C" sg_status sg_autotune(sg_volume* vol, int32_t n_views, const sg_view*
         if (dim == 3) c.stage_bytes = vals[dim][k];
         if (dim == 4) c.persistent = vals[dim][k];
         if (dim == 3 && c.gather) continue;  // the staging size is moot for gather
-        if (c.bt_log < c.tile_log || lds_bytes(v, c) > 160 * 1024) continue;
+        if (c.bt_log < c.tile_log || lds_budget(v, c) > 160 * 1024) continue;
         if (std::memcmp(&c, &cur, sizeof(c)) == 0) continue;
         cand.push_back(c);
       }

@@ -456,22 +456,33 @@ __device__ __forceinline__ float sample_tau(const Ray& r, int k) {
 // holds per entry k the value t[k] and the difference t[k+1] - t[k] (zero
 // for the last entry), so each interpolation is one fused multiply-add,
 // fma(w, t[k+1] - t[k], t[k]): the same operations, in the same FP32
-// rounding, as lerpf(t[k], t[k+1], w).
+// rounding, as lerpf(t[k], t[k+1], w). With several channels it holds the
+// values alone and the difference is formed at the look-up (see tf_pairs).
+template <int CH>
 __device__ __forceinline__ float4 tf_lookup(const RenderArgs& a, const float4* s_tf, int ch,
                                             float val, float scale, float bias) {
   float u = fmaf(val, scale, bias);
   u = __builtin_amdgcn_fmed3f(u, 0.0f, (float)(a.tf_n - 1));  // clamp (u is finite)
   const int k0 = (int)u;
   const float wt = __builtin_amdgcn_fractf(u);  // = u - k0 exactly, u >= 0
-  const float4 t = s_tf[2 * (ch * a.tf_n + k0)];
-  const float4 d = s_tf[2 * (ch * a.tf_n + k0) + 1];
+  float4 t, d;
+  if (tf_pairs(CH)) {
+    t = s_tf[2 * (ch * a.tf_n + k0)];
+    d = s_tf[2 * (ch * a.tf_n + k0) + 1];
+  } else {
+    const float4* p = s_tf + ch * (a.tf_n + 1) + k0;
+    t = p[0];
+    const float4 n = p[1];
+    d = make_float4(n.x - t.x, n.y - t.y, n.z - t.z, n.w - t.w);
+  }
   return make_float4(fmaf(wt, d.x, t.x), fmaf(wt, d.y, t.y), fmaf(wt, d.z, t.z),
                      fmaf(wt, d.w, t.w));
 }
 
+template <int CH>
 __device__ __forceinline__ float4 tf_lookup(const RenderArgs& a, const float4* s_tf, int ch,
                                             float val) {
-  return tf_lookup(a, s_tf, ch, val, a.tf_scale[ch], a.tf_bias[ch]);
+  return tf_lookup<CH>(a, s_tf, ch, val, a.tf_scale[ch], a.tf_bias[ch]);
 }
 
 // The transfer-table windows of a run of samples, the offsets held in
@@ -557,7 +568,7 @@ __device__ __forceinline__ Shade shade_ea(const Ray& r, const RenderArgs& a, con
   for (int ch = 0; ch < CH; ++ch) {
     const float val = fetch(ch, ix, iy, iz, fx, fy, fz);
     if (STATS) mark_microblocks(r, a, ch, ix, iy, iz, mb_key[ch]);
-    const float4 c = tf_lookup(a, s_tf, ch, val, w.scale[ch], w.bias[ch]);
+    const float4 c = tf_lookup<CH>(a, s_tf, ch, val, w.scale[ch], w.bias[ch]);
     if (CH == 1) {
       z = Shade{c.w, c.x, c.y, c.z};
     } else {
@@ -650,7 +661,7 @@ __device__ __forceinline__ bool sample_step(Ray& r, const RenderArgs& a, const f
       r.vmax[ch] = fmaxf(r.vmax[ch], val);
       continue;
     }
-    const float4 c = tf_lookup(a, s_tf, ch, val, w.scale[ch], w.bias[ch]);
+    const float4 c = tf_lookup<CH>(a, s_tf, ch, val, w.scale[ch], w.bias[ch]);
     er += c.x;
     eg += c.y;
     eb += c.z;
@@ -722,7 +733,7 @@ __device__ __forceinline__ bool write_pixel(Ray& r, const RenderArgs& a, const V
     // the summed emission of the channel maxima
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
-      const float4 c = tf_lookup(a, s_tf, ch, r.vmax[ch]);
+      const float4 c = tf_lookup<CH>(a, s_tf, ch, r.vmax[ch]);
       r.Cr += c.x;
       r.Cg += c.y;
       r.Cb += c.z;
@@ -847,11 +858,16 @@ __device__ __forceinline__ bool next_tile(const RenderArgs& a, TileLane& tl) {
 
 // The workgroup's LDS copy of the transfer tables: per channel and entry
 // k < tf_n, t[k] and t[k+1] - t[k] (the device table repeats its last
-// entry, so the last difference is zero).
+// entry, so the last difference is zero); or the device table as it is.
 template <int CH>
 __device__ __forceinline__ void load_tf(const RenderArgs& a, float4* s_tf) {
   const int ntf = CH * a.tf_n;
   const float4* tf = reinterpret_cast<const float4*>(a.tf);
+  if (!tf_pairs(CH)) {
+    for (int i = threadIdx.x; i < CH * (a.tf_n + 1); i += blockDim.x) s_tf[i] = tf[i];
+    __syncthreads();
+    return;
+  }
   for (int i = threadIdx.x; i < ntf; i += blockDim.x) {
     const int ch = i / a.tf_n, k = i - ch * a.tf_n;
     const float4 t0 = tf[ch * (a.tf_n + 1) + k], t1 = tf[ch * (a.tf_n + 1) + k + 1];
@@ -955,8 +971,8 @@ __device__ __forceinline__ void gather_run(Ray& r, const RenderArgs& a, const fl
       const Stencil n0 = stencil_at<T, MB>(r, a, slot, t2);
       const Stencil n1 = stencil_at<T, MB>(r, a, slot, t3);
       __builtin_amdgcn_sched_barrier(0);
-      const float4 e0 = tf_lookup(a, s_tf, 0, stencil_value(c0), w.scale[0], w.bias[0]);
-      const float4 e1 = tf_lookup(a, s_tf, 0, stencil_value(c1), w.scale[0], w.bias[0]);
+      const float4 e0 = tf_lookup<1>(a, s_tf, 0, stencil_value(c0), w.scale[0], w.bias[0]);
+      const float4 e1 = tf_lookup<1>(a, s_tf, 0, stencil_value(c1), w.scale[0], w.bias[0]);
       go = shade_step<DEPTH>(r, a, e0) && r.k <= kf;
       if (go) go = shade_step<DEPTH>(r, a, e1) && r.k <= kf;
       __builtin_amdgcn_sched_barrier(0);
@@ -1644,7 +1660,7 @@ __global__ __launch_bounds__(256) void raycast_staged(RenderArgs a) {
   load_tf<CH>(a, s_tf);
   // the wave's staging space (the wave index is the same for all its lanes:
   // scalar registers)
-  T* stage = reinterpret_cast<T*>(reinterpret_cast<uint8_t*>(smem + 2 * CH * a.tf_n) +
+  T* stage = reinterpret_cast<T*>(reinterpret_cast<uint8_t*>(smem + tf_lds_entries(CH, a.tf_n)) +
                                   uniform((int)(threadIdx.x >> 6)) * a.stage_bytes);
   // no workgroup barrier follows: the waves work independently from here
   if (!LOOP) {

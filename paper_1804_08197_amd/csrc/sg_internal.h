@@ -309,6 +309,18 @@ sg_status cutmap_launch(const Volume* v, const ViewDev* dviews, int n_views, int
 sg_status cutmap_run(const Volume* v, const ViewDev* dviews, int n_views, int bias, bool lod,
                      int timepoint, int32_t* cutmap, const InlineViews& iv, hipStream_t s);
 
+// The ray caster's LDS copy of the transfer tables, in float4: one channel
+// keeps value and difference per entry (four subtractions fewer per sample;
+// that kernel is bound by its vector instructions), several channels the
+// values alone: the staged kernel's workgroups per CU are then set by LDS,
+// and half the table makes room for one more (three channels of 256 entries
+// with 8 KiB of staging per wave: 56 -> 44 KiB, two -> three; stereo frame of
+// three-channel cells 4546 -> 3800 us).
+__host__ __device__ constexpr bool tf_pairs(int channels) { return channels == 1; }
+__host__ __device__ constexpr int tf_lds_entries(int channels, int n) {
+  return tf_pairs(channels) ? 2 * channels * n : channels * (n + 1);
+}
+
 struct RenderArgs {
   const uint8_t* pool;
   int64_t slot_bytes;
