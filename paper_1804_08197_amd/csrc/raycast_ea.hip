@@ -9,4 +9,12 @@ const void* raycast_kernel_absorption(int bpv, int channels, bool stats, bool ga
   return model_kernel<kModelAbsorption>(bpv, channels, stats, gather, loop, mb);
 }
 
+const void* raycast_kernel_split(int bpv, bool mb) {
+  if (bpv == 1)
+    return mb ? reinterpret_cast<const void*>(raycast_gather_split<uint8_t, true>)
+              : reinterpret_cast<const void*>(raycast_gather_split<uint8_t, false>);
+  return mb ? reinterpret_cast<const void*>(raycast_gather_split<uint16_t, true>)
+            : reinterpret_cast<const void*>(raycast_gather_split<uint16_t, false>);
+}
+
 }  // namespace sg

@@ -116,7 +116,14 @@ struct ViewDev {
   double lens[4];      // k1, k2, cx, cy
   int32_t lens_on;
   uint8_t* tile_any;   // per 8x8-pixel block content flag or NULL
+  // pixels [x0, x1] x [y0, y1] outside of which no ray meets the volume box
+  // (the whole image where no such bound is known)
+  int32_t hit[4];
 };
+// May the ray of pixel (px, py) meet the volume box?
+__host__ __device__ __forceinline__ bool may_hit(const ViewDev& V, int px, int py) {
+  return px >= V.hit[0] && px <= V.hit[1] && py >= V.hit[2] && py <= V.hit[3];
+}
 
 // Up to kInlineViews view records travel inside the cut-map kernel's
 // arguments; its first workgroup writes them to the device view table that
@@ -186,6 +193,7 @@ struct Volume {
   int64_t cutmap_cap = 0;
   uint8_t* view_dev = nullptr;
   InlineViews inline_views{};  // the last prepare_views' table when it is small
+  int64_t hit_tiles = 0;       // its 8x8-pixel tiles that may meet the volume
   int64_t view_cap = 0;
   // pinned staging for small uploads (view tables): a ring, so the host can
   // enqueue several renders ahead of the device
@@ -379,6 +387,7 @@ struct RenderArgs {
   double planes[4][4];  // plane j keeps (n . p) + w <= 0: (nx, ny, nz, w)
   double roi[6];        // region of interest lo xyz, hi xyz
   const int32_t* enable;  // NULL, or a device flag: 0 = every workgroup returns at once
+  int32_t split;          // gather, one channel, emission-absorption: four lanes to a ray
   // slabs that cannot contribute are passed over (staged kernel): the block
   // maxima (Volume::bmax; NULL: every slab is sampled) and, per channel, the
   // largest voxel value without extinction and without colour (dim[c][2],
@@ -401,6 +410,7 @@ sg_status raycast_launch(Volume* v, RenderArgs& a, bool stats, Launch* out);
 // micro-block pool slots.
 const void* raycast_kernel_absorption(int bpv, int channels, bool stats, bool gather,
                                       bool loop, bool mb);
+const void* raycast_kernel_split(int bpv, bool mb);
 const void* raycast_kernel_emission(int bpv, int channels, bool stats, bool gather, bool loop,
                                     bool mb);
 const void* raycast_kernel_mip(int bpv, int channels, bool stats, bool gather, bool loop,
