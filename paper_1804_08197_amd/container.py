@@ -234,9 +234,10 @@ class HostBrickStore:
         if not len(ids):
             return 0
         L, b = decode_ids(ids)
-        groups = defaultdict(list)
-        for i in np.lexsort((ids, -L)):
-            groups[(int(tps[i]), int(L[i]))].append(b[i])
-        for (t, lev), cs in groups.items():
-            self._put(t, lev, np.asarray(cs, dtype=np.int64), stream)
+        order = np.lexsort((ids, -L))  # coarse levels first
+        L, b, t = L[order], b[order], np.asarray(tps)[order]
+        key = t.astype(np.int64) * self.levels + L
+        for k in key[np.sort(np.unique(key, return_index=True)[1])]:
+            self._put(int(k) // self.levels, int(k) % self.levels,
+                      b[key == k].astype(np.int64), stream)
         return len(ids)

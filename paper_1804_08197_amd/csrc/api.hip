@@ -92,8 +92,12 @@ void free_all(Volume* v) {
   if (v->queue) hipFree(v->queue);
   if (v->stamp) hipFree(v->stamp);
   if (v->req_flags) hipFree(v->req_flags);
-  if (v->req_list) hipFree(v->req_list);
   if (v->req_count) hipFree(v->req_count);
+  if (v->put_stage) hipFree(v->put_stage);
+  if (v->put_meta) hipFree(v->put_meta);
+  if (v->put_meta_host) hipHostFree(v->put_meta_host);
+  if (v->put_copied) hipEventDestroy(v->put_copied);
+  if (v->put_done) hipEventDestroy(v->put_done);
   hipFree(v->cutmap);
   hipFree(v->view_dev);
   hipFree(v->mb_bits);
@@ -196,12 +200,13 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
   if (v->cache &&
       !(alloc((void**)&v->stamp, v->slots * 4) &&
         alloc((void**)&v->req_flags, (((int64_t)d->timepoints * nodes + 31) / 32) * 4) &&
-        alloc((void**)&v->req_list, (int64_t)kReqCap * 4) && alloc((void**)&v->req_count, 4))) {
+        alloc((void**)&v->req_count, (int64_t)(kReqHead + kReqCap) * 4))) {
     free_all(v);
     delete h;
     (void)hipGetLastError();
     return fail(SG_ERR_OUT_OF_MEMORY, "device allocation failed (cache tables)");
   }
+  if (v->cache) v->req_list = v->req_count + kReqHead;
   // the block maxima (1/64 or 1/32 of the pool) only speed renders up: a
   // volume that leaves no room for them goes without
   v->bmax_stride = v->slot_bytes >> bmax_shift(v->M != 0);
@@ -222,6 +227,13 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
       delete h;
       return fail(SG_ERR_DEVICE, "event creation failed");
     }
+  if (v->cache &&
+      (hipEventCreateWithFlags(&v->put_copied, hipEventDisableTiming) != hipSuccess ||
+       hipEventCreateWithFlags(&v->put_done, hipEventDisableTiming) != hipSuccess)) {
+    free_all(v);
+    delete h;
+    return fail(SG_ERR_DEVICE, "event creation failed");
+  }
   // page table: every node resident with slot = (t * C + c) * nodes + node,
   // or (cache) nothing resident and every slot free
   std::vector<int32_t> page((size_t)v->entries);
@@ -422,7 +434,8 @@ sg_status sg_get_kernel_timing(sg_volume* vol, int32_t* renders, double* cutmap_
 sg_status sg_volume_memory(const sg_volume* vol, uint64_t* bytes) {
   if (!vol || !bytes) return fail(SG_ERR_INVALID_ARG, "sg_volume_memory: NULL argument");
   *bytes = vol->v.bytes + (uint64_t)vol->v.cutmap_cap * 4 + (uint64_t)vol->v.view_cap +
-           (uint64_t)vol->v.mb_words * 4;
+           (uint64_t)vol->v.mb_words * 4 + (uint64_t)vol->v.put_stage_cap +
+           (uint64_t)vol->v.put_meta_cap * 4;
   return SG_OK;
 }
 

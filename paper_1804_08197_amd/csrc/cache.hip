@@ -147,6 +147,86 @@ using namespace sg;
 
 namespace {
 
+// Room for n entries of a call's tables.
+sg_status put_meta_room(Volume* v, int64_t n) {
+  if (n <= v->put_meta_cap) return SG_OK;
+  if (v->put_meta) SG_HIP(hipFree(v->put_meta));  // (waits for what uses it)
+  if (v->put_meta_host) SG_HIP(hipHostFree(v->put_meta_host));
+  v->put_meta = v->put_meta_host = nullptr;
+  v->put_meta_cap = 0;
+  const int64_t cap = std::max<int64_t>(2 * n, 16384);
+  if (hipMalloc((void**)&v->put_meta, (size_t)cap * 4) != hipSuccess ||
+      hipHostMalloc((void**)&v->put_meta_host, (size_t)cap * 4, hipHostMallocDefault) !=
+          hipSuccess) {
+    (void)hipGetLastError();
+    return fail(SG_ERR_OUT_OF_MEMORY, "sg_cache_put: allocation of the put's tables failed");
+  }
+  v->put_meta_cap = cap;
+  return SG_OK;
+}
+
+// Room for the regions of up to n bricks (*batch: how many fit at a time),
+// fewer where memory is short. Kept from put to put: a buffer taken from the
+// stream's pool for each put went back to the system at the next
+// synchronisation, and mapping up to 83 MB anew took 0.3 ms of a put.
+sg_status put_stage_room(Volume* v, int64_t region, int64_t n, int64_t* batch) {
+  int64_t want = std::min(n, std::max<int64_t>(1, kPutStage / region));
+  if (want * region > v->put_stage_cap) {
+    if (v->put_stage) SG_HIP(hipFree(v->put_stage));  // (waits for what uses it)
+    v->put_stage = nullptr;
+    v->put_stage_cap = 0;
+    while (hipMalloc((void**)&v->put_stage, (size_t)(want * region)) != hipSuccess) {
+      (void)hipGetLastError();
+      v->put_stage = nullptr;
+      if (want == 1)
+        return fail(SG_ERR_OUT_OF_MEMORY, "sg_cache_put: allocation of the staging buffer failed");
+      want /= 2;
+    }
+    v->put_stage_cap = want * region;
+  }
+  *batch = std::min(n, v->put_stage_cap / region);
+  return SG_OK;
+}
+
+// Copy k regions from b0 on to the staging buffer.
+sg_status send_regions(Volume* v, int64_t region, int64_t b0, int64_t k, const void* src,
+                       const void* const* srcs, hipStream_t s) {
+  if (!srcs) {
+    SG_HIP(hipMemcpyAsync(v->put_stage, (const uint8_t*)src + region * b0, (size_t)(region * k),
+                          hipMemcpyHostToDevice, s));
+    return SG_OK;
+  }
+  // one copy per run of regions that lie back to back in the source
+  for (int64_t i = 0; i < k;) {
+    int64_t j = i + 1;
+    while (j < k && (const uint8_t*)srcs[b0 + j] == (const uint8_t*)srcs[b0 + j - 1] + region) ++j;
+    SG_HIP(hipMemcpyAsync(v->put_stage + region * i, srcs[b0 + i], (size_t)(region * (j - i)),
+                          hipMemcpyDefault, s));
+    i = j;
+  }
+  return SG_OK;
+}
+
+// Store the regions at dsrc in their slots.
+void launch_put(Volume* v, int n, const int32_t* d_slot, const int32_t* d_ent, const void* dsrc,
+                hipStream_t s) {
+  const int per = groups_per_brick(n, v->Mb * v->Mb * v->Mb * 16);
+  const dim3 grid((unsigned)((int64_t)n * per));
+  const bool wide = v->bpv == 2 && reinterpret_cast<uintptr_t>(dsrc) % 4 == 0;
+#define SG_PUT(T, MB, WIDE)                                                                    \
+  hipLaunchKernelGGL((put_kernel<T, MB, WIDE>), grid, dim3(256), 0, s, v->pool, v->slot_bytes, \
+                     d_slot, d_ent, (const T*)dsrc, v->range, v->dark, v->bmax, v->bmax_stride, per,    \
+                     v->S, v->Sx, v->Mb)
+  if (v->bpv == 1) {
+    if (v->M) SG_PUT(uint8_t, true, false); else SG_PUT(uint8_t, false, false);
+  } else if (wide) {
+    if (v->M) SG_PUT(uint16_t, true, true); else SG_PUT(uint16_t, false, true);
+  } else {
+    if (v->M) SG_PUT(uint16_t, true, false); else SG_PUT(uint16_t, false, false);
+  }
+#undef SG_PUT
+}
+
 // Both put entry points: the regions come from one buffer (src, host or
 // device) or from one pointer per brick (srcs, any memory; each copied by
 // its own DMA into the staging buffer).
@@ -186,17 +266,44 @@ sg_status put_impl(sg_volume* vol, int32_t channel, int32_t timepoint, int32_t l
   if (!guard.ok) return fail(SG_ERR_DEVICE, "cannot select device");
   hipStream_t s = (hipStream_t)hip_stream;
 
-  // slots: the brick's own if resident, else a free one, else the oldest
-  // evictable one (min-heap over the stamps of the last renders)
+  // a put waits for its copies and so cannot be recorded
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap != hipStreamCaptureStatusNone)
+    return fail(SG_ERR_DEVICE, "sg_cache_put: the stream is being captured");
+
+  // room for what travels, before the tables change
+  const int64_t region = (int64_t)v->S * v->S * v->S * v->bpv;
+  const bool staged = srcs || !src_on_device;
+  int64_t batch = n;  // bricks on their way at a time
   int need = 0;
   for (int64_t e : ent)
     if (v->page_host[(size_t)e] < 0) ++need;
+  const bool evict = need > (int)v->free_slots.size();
+  sg_status st = put_meta_room(v, std::max<int64_t>(6 * (int64_t)n, evict ? v->slots : 0));
+  if (st != SG_OK) return st;
+  if (staged && (st = put_stage_room(v, region, n, &batch)) != SG_OK) return st;
+  // The stamps come back before the regions leave, and the regions leave
+  // before the host chooses slots by the stamps. A put on another stream than
+  // the last one finds that one's scratch free. (Two timepoints of 384x384x256
+  // with two channels through a cache of one, 380 MB in 12 puts and 6 frames:
+  // 13.4 -> 10.8 ms, of which the bus needs 6.7 and the kernels 3.0.)
+  if (v->put_pending) SG_HIP(hipStreamWaitEvent(s, v->put_done, 0));
+  v->put_pending = true;
+  if (evict) {
+    SG_HIP(hipMemcpyAsync(v->put_meta_host, v->stamp, (size_t)v->slots * 4, hipMemcpyDeviceToHost, s));
+    SG_HIP(hipEventRecord(v->put_copied, s));
+  }
+  if (staged && (st = send_regions(v, region, 0, std::min<int64_t>(batch, n), src, srcs, s)) != SG_OK)
+    return st;
+
+  // slots: the brick's own if resident, else a free one, else the oldest
+  // evictable one (min-heap over the stamps of the last renders)
   std::vector<int32_t> slot((size_t)n, -1);
   std::vector<int32_t> pidx, pval;  // page updates
-  if (need > (int)v->free_slots.size()) {
-    SG_HIP(hipStreamSynchronize(s));
-    std::vector<uint32_t> stamp((size_t)v->slots);
-    SG_HIP(hipMemcpy(stamp.data(), v->stamp, (size_t)v->slots * 4, hipMemcpyDeviceToHost));
+  if (evict) {
+    SG_HIP(hipEventSynchronize(v->put_copied));
+    const uint32_t* stamp = reinterpret_cast<const uint32_t*>(v->put_meta_host);
     std::vector<char> keep((size_t)v->entries, 0);
     for (int64_t e : ent) keep[(size_t)e] = 1;
     typedef std::pair<uint32_t, int32_t> Item;  // (stamp, slot): oldest first
@@ -206,10 +313,12 @@ sg_status put_impl(sg_volume* vol, int32_t channel, int32_t timepoint, int32_t l
       if (e < 0 || keep[(size_t)e] || is_top(v, e)) continue;
       heap.push(Item(stamp[(size_t)sl], (int32_t)sl));
     }
-    if ((int64_t)heap.size() + (int64_t)v->free_slots.size() < need)
+    if ((int64_t)heap.size() + (int64_t)v->free_slots.size() < need) {
+      SG_HIP(hipStreamSynchronize(s));  // the regions are on their way
       return fail(SG_ERR_OUT_OF_MEMORY,
                   "sg_cache_put: more bricks than the cache can free (top-level nodes are "
                   "never evicted)");
+    }
     while (need > (int)v->free_slots.size()) {
       const int32_t sl = heap.top().second;
       heap.pop();
@@ -237,62 +346,34 @@ sg_status put_impl(sg_volume* vol, int32_t channel, int32_t timepoint, int32_t l
   }
   v->uploads += n;
 
-  // device side: regions, page updates, ranges
-  const int64_t S3 = (int64_t)v->S * v->S * v->S;
-  const int64_t data_bytes = S3 * v->bpv * n;
-  const int64_t meta = 4 * ((int64_t)2 * n + 2 * (int64_t)pidx.size());
-  const int64_t meta_pad = ((meta + 255) / 256) * 256;
-  const bool staged = srcs || !src_on_device;
-  uint8_t* tmp = nullptr;
-  SG_HIP(hipMallocAsync((void**)&tmp, (size_t)(meta_pad + (staged ? data_bytes : 0)), s));
-  std::vector<int32_t> host_meta;
-  host_meta.insert(host_meta.end(), slot.begin(), slot.end());
-  for (int64_t e : ent) host_meta.push_back((int32_t)e);
-  host_meta.insert(host_meta.end(), pidx.begin(), pidx.end());
-  host_meta.insert(host_meta.end(), pval.begin(), pval.end());
-  SG_HIP(hipMemcpyAsync(tmp, host_meta.data(), host_meta.size() * 4, hipMemcpyHostToDevice, s));
-  const void* dsrc = src;
-  if (srcs) {
-    // one copy per run of regions that lie back to back in the source
-    const size_t region = (size_t)(S3 * v->bpv);
-    for (int32_t i = 0; i < n;) {
-      int32_t j = i + 1;
-      while (j < n && (const uint8_t*)srcs[j] == (const uint8_t*)srcs[j - 1] + region) ++j;
-      SG_HIP(hipMemcpyAsync(tmp + meta_pad + region * (size_t)i, srcs[i],
-                            region * (size_t)(j - i), hipMemcpyDefault, s));
-      i = j;
-    }
-    dsrc = tmp + meta_pad;
-  } else if (!src_on_device) {
-    SG_HIP(hipMemcpyAsync(tmp + meta_pad, src, (size_t)data_bytes, hipMemcpyHostToDevice, s));
-    dsrc = tmp + meta_pad;
-  }
-  SG_HIP(hipStreamSynchronize(s));  // host buffers consumed before returning
-  const int32_t* d_slot = reinterpret_cast<const int32_t*>(tmp);
+  // device side: regions, page updates, ranges; only the copies are waited for
+  const int np = (int)pidx.size();
+  int32_t* const m = v->put_meta_host;
+  std::copy(slot.begin(), slot.end(), m);
+  for (int32_t i = 0; i < n; ++i) m[n + i] = (int32_t)ent[(size_t)i];
+  std::copy(pidx.begin(), pidx.end(), m + 2 * n);
+  std::copy(pval.begin(), pval.end(), m + 2 * n + np);
+  const int32_t* d_slot = v->put_meta;
   const int32_t* d_ent = d_slot + n;
   const int32_t* d_pidx = d_ent + n;
-  const int32_t* d_pval = d_pidx + pidx.size();
-  const int np = (int)pidx.size();
-  hipLaunchKernelGGL(put_tables_kernel, dim3((unsigned)((std::max(n, np) + 255) / 256)), dim3(256),
-                     0, s, v->stamp, d_slot, d_ent, n, v->frame, v->range, v->dark, v->page, d_pidx, d_pval,
-                     np);
-  const int per = groups_per_brick(n, v->Mb * v->Mb * v->Mb * 16);
-  const dim3 grid((unsigned)((int64_t)n * per));
-  const bool wide = v->bpv == 2 && reinterpret_cast<uintptr_t>(dsrc) % 4 == 0;
-#define SG_PUT(T, MB, WIDE)                                                                    \
-  hipLaunchKernelGGL((put_kernel<T, MB, WIDE>), grid, dim3(256), 0, s, v->pool, v->slot_bytes, \
-                     d_slot, d_ent, (const T*)dsrc, v->range, v->dark, v->bmax, v->bmax_stride, per,    \
-                     v->S, v->Sx, v->Mb)
-  if (v->bpv == 1) {
-    if (v->M) SG_PUT(uint8_t, true, false); else SG_PUT(uint8_t, false, false);
-  } else if (wide) {
-    if (v->M) SG_PUT(uint16_t, true, true); else SG_PUT(uint16_t, false, true);
-  } else {
-    if (v->M) SG_PUT(uint16_t, true, false); else SG_PUT(uint16_t, false, false);
+  const int32_t* d_pval = d_pidx + np;
+  for (int64_t b0 = 0; b0 < n; b0 += batch) {
+    const int64_t k = std::min<int64_t>(batch, n - b0);
+    const void* dsrc = staged ? v->put_stage : (const uint8_t*)src;
+    if (staged && b0 > 0 && (st = send_regions(v, region, b0, k, src, srcs, s)) != SG_OK)
+      return st;
+    if (b0 == 0)
+      SG_HIP(hipMemcpyAsync(v->put_meta, m, ((size_t)n + (size_t)np) * 8, hipMemcpyHostToDevice, s));
+    if (b0 + k == n) SG_HIP(hipEventRecord(v->put_copied, s));
+    if (b0 == 0)
+      hipLaunchKernelGGL(put_tables_kernel, dim3((unsigned)((std::max(n, np) + 255) / 256)),
+                         dim3(256), 0, s, v->stamp, d_slot, d_ent, n, v->frame, v->range, v->dark,
+                         v->page, d_pidx, d_pval, np);
+    launch_put(v, (int)k, d_slot + b0, d_ent + b0, dsrc, s);
+    SG_HIP(hipGetLastError());
   }
-#undef SG_PUT
-  SG_HIP(hipGetLastError());
-  SG_HIP(hipFreeAsync(tmp, s));
+  SG_HIP(hipEventRecord(v->put_done, s));
+  SG_HIP(hipEventSynchronize(v->put_copied));  // host buffers consumed before returning
   v->empty_dirty = true;
   return SG_OK;
 }
@@ -322,17 +403,24 @@ extern "C" sg_status sg_cache_requests(sg_volume* vol, uint64_t* ids, int32_t* t
   DeviceGuard guard(v->d.device);
   if (!guard.ok) return fail(SG_ERR_DEVICE, "cannot select device");
   hipStream_t s = (hipStream_t)hip_stream;
-  uint32_t count = 0;
-  SG_HIP(hipMemcpyAsync(&count, v->req_count, 4, hipMemcpyDeviceToHost, s));
+  // the count and the first of the list together; the rest only if there is more
+  sg_status st = put_meta_room(v, 4096);
+  if (st != SG_OK) return st;
+  const int32_t first = (int32_t)std::min<int64_t>(4096, v->put_meta_cap - kReqHead);
+  SG_HIP(hipMemcpyAsync(v->put_meta_host, v->req_count, ((size_t)kReqHead + (size_t)first) * 4,
+                        hipMemcpyDeviceToHost, s));
   SG_HIP(hipStreamSynchronize(s));
+  const uint32_t count = (uint32_t)v->put_meta_host[0];
   const int32_t m = (int32_t)std::min<uint32_t>(count, (uint32_t)kReqCap);
   if (m > *n) {
     *n = m;
     return fail(SG_ERR_INVALID_ARG, "sg_cache_requests: capacity too small");
   }
-  std::vector<uint32_t> list((size_t)std::max(m, 1));
-  if (m > 0)
-    SG_HIP(hipMemcpyAsync(list.data(), v->req_list, (size_t)m * 4, hipMemcpyDeviceToHost, s));
+  std::vector<uint32_t> list((size_t)m);
+  std::copy_n(v->put_meta_host + kReqHead, std::min(m, first), list.begin());
+  if (m > first)
+    SG_HIP(hipMemcpyAsync(list.data() + first, v->req_list + first, (size_t)(m - first) * 4,
+                          hipMemcpyDeviceToHost, s));
   const int64_t words = ((int64_t)v->d.timepoints * v->nodes + 31) / 32;
   if (count > (uint32_t)kReqCap) {
     // the list overflowed: some set bits are not listed, so clear them all

@@ -214,10 +214,22 @@ struct Volume {
   std::vector<int32_t> free_slots;
   uint32_t* stamp = nullptr;        // [slots] frame of last use
   uint32_t* req_flags = nullptr;    // [T * nodes] bits: requested since last read
-  uint32_t* req_list = nullptr;     // [kReqCap] requested t * nodes + node
-  uint32_t* req_count = nullptr;
+  uint32_t* req_count = nullptr;    // one word, then kReqHead - 1 unused ones
+  uint32_t* req_list = nullptr;     // [kReqCap] requested t * nodes + node, in
+                                    // the same allocation as req_count
   uint32_t frame = 0;
   int64_t uploads = 0, evictions = 0;
+  // scratch of the cache calls, kept from call to call: host regions on their
+  // way to the slots (at most kPutStage bytes or one region), and the small
+  // tables of a call (device, and page-locked host memory)
+  uint8_t* put_stage = nullptr;
+  int64_t put_stage_cap = 0;
+  int32_t* put_meta = nullptr;
+  int32_t* put_meta_host = nullptr;
+  int64_t put_meta_cap = 0;         // entries of each
+  hipEvent_t put_copied = nullptr;  // the last put's copies from the host ran
+  hipEvent_t put_done = nullptr;    // the last put's kernels ran
+  bool put_pending = false;
   // launch configuration of the ray caster, and the persistent grid's queues
   LaunchConfig cfg;
   uint32_t* queue = nullptr;  // 8 counters
@@ -229,6 +241,9 @@ struct Volume {
 
 // Capacity of the request list of a cache volume.
 constexpr int kReqCap = 1 << 20;
+constexpr int kReqHead = 64;  // words before the list (its count is the first)
+// Most bytes of host regions a put keeps on the device at a time.
+constexpr int64_t kPutStage = 128 << 20;
 
 // Record an event from the volume's pool on `s` (timing mode only).
 sg_status timing_mark(Volume* v, hipStream_t s);
