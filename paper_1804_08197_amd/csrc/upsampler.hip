@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/sg_upsampler.h"
@@ -987,13 +988,17 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* o, const bf16* x
 //    of x meets the three rows of g around it at three column shifts: nine
 //    products for 8 + 10 loads per lane. The rows of g are kept while the
 //    wave walks down its column.
-//  * 8 input channels: the rows of A are (tap, ci), three tiles of 32, x
-//    shifted per lane.
+//  * 8 input channels: the rows of A are (dy, ci), x from the three rows
+//    around g's, and g is shifted by column again: three products for the
+//    same loads.
 // Each wave keeps all its sums in registers (144 for 32 channels); the
-// waves' sums are folded through LDS in a fixed order. Bound by memory and
-// load latency: 128 bytes per pixel against 2 x 9 x 32 x 32 flop; 16 x 128 x
-// 128 pixels 37 us (32 channels; 466 as FP32 multiply-adds on the vector
-// units) and 42 us (8 channels; 161).
+// waves' sums are folded through LDS in a fixed order. Bound by memory
+// latency (128 bytes per pixel against 2 x 9 x 32 x 32 flop): the loads of
+// two (32 channels; the registers are full) or three rows are in flight
+// while a row is multiplied, and all of a column's first rows go out
+// together. 16 x 128 x 128 pixels: 24 us (32 channels; 37 with one row in
+// flight, 466 as FP32 multiply-adds on the vector units) and 12 us (8
+// channels; 42 and 161).
 constexpr int kWgWaves = 8;
 __device__ __forceinline__ uint32_t pair16(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
 __device__ __forceinline__ bf16x8 frag(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
@@ -1003,9 +1008,9 @@ __device__ __forceinline__ bf16x8 frag(uint32_t a, uint32_t b, uint32_t c, uint3
 // Folds the waves' accumulators (T tiles of 32 x 32, register layout of the
 // product) and bias sums, and writes the workgroup's partial sums: rows
 // below `rows` of the T tiles, then the bias. LDS: 4 T tiles and the bias.
-template <int T>
-__device__ __forceinline__ void wgrad_out(floatx16 (&acc)[T], float bacc, int rows, float* lds,
-                                          float* out) {
+template <int CIN, int T>
+__device__ __forceinline__ void wgrad_out(floatx16 (&acc)[T], float bacc, float* lds, float* out) {
+  constexpr int rows = 9 * CIN;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float* sb = lds + 4 * T * 1024;  // [waves][64]
   // a tile in LDS: 16-byte groups of four registers, lane by lane
@@ -1038,10 +1043,12 @@ __device__ __forceinline__ void wgrad_out(floatx16 (&acc)[T], float bacc, int ro
   __syncthreads();
   if (wave < 4) put(wave);
   __syncthreads();
-  // element (row, co) of the tiles: lane (row / 4 % 2) 32 + co, register
-  // 4 (row / 8 % 4) + row % 4 of tile row / 32
+  // element (row r, co) of a tile: lane (r / 4 % 2) 32 + co, register
+  // 4 (r / 8) + r % 4. Tap (dy, dx), channel ci: 32 channels: row ci of tile
+  // 3 dy + dx; 8 channels: row 8 dy + ci of tile dx
   for (int e = threadIdx.x; e < rows * kCh; e += 64 * kWgWaves) {
-    const int row = e >> 5, co = e & 31, t = row >> 5, r = row & 31;
+    const int row = e >> 5, co = e & 31, tap = row / CIN, ci = row % CIN;
+    const int t = CIN == 32 ? tap : tap % 3, r = CIN == 32 ? ci : tap / 3 * 8 + ci;
     const int k = (t * 4 + (r >> 3)) * 256 + (((r >> 2) & 1) * 32 + co) * 4 + (r & 3);
     out[e] = (lds[k] + lds[k + T * 1024]) + (lds[k + 2 * T * 1024] + lds[k + 3 * T * 1024]);
   }
@@ -1054,14 +1061,19 @@ __device__ __forceinline__ void wgrad_out(floatx16 (&acc)[T], float bacc, int ro
 }
 constexpr size_t wgrad_lds(int tiles) { return (size_t)(4 * tiles * 1024 + kWgWaves * 64) * 4; }
 
+// A row piece's loads: 8 pixels of x and 10 of g around them, as stored.
+struct WgradRow {
+  uint32_t x[8], g[10];
+};
+
 template <int CIN>
 __global__ __launch_bounds__(64 * kWgWaves, 2) void wgrad_kernel(const bf16* __restrict__ xb,
                                                               const bf16* __restrict__ gb, int N,
                                                               int H, int W, float* part) {
   extern __shared__ float wgrad_smem[];
   constexpr int T = CIN == 32 ? 9 : 3;
-  const uint16_t* x = reinterpret_cast<const uint16_t*>(xb);
-  const uint16_t* g = reinterpret_cast<const uint16_t*>(gb);
+  const char* x = reinterpret_cast<const char*>(xb);
+  const char* g = reinterpret_cast<const char*>(gb);
   const int lane = threadIdx.x & 63, ch = lane & 31, half = lane >> 5;
   const Pieces pc = wave_pieces(N, H, W, 16);
   floatx16 acc[T];
@@ -1073,121 +1085,159 @@ __global__ __launch_bounds__(64 * kWgWaves, 2) void wgrad_kernel(const bf16* __r
   int64_t colno = pc.s0 / H;
   int y = (int)(pc.s0 - colno * H);
   int64_t img = 0;
-  int x0 = 0;  // the lane's first pixel of the piece
-  if (CIN == 32) {
-    // per pixel x0 - 1 .. x0 + 8: element offset from the row, clamped into it
-    int off[10];
-    auto raw = [&](const uint16_t* p, int yy, int k) -> uint32_t {
-      const uint32_t v = p[(img + (int64_t)yy * W) * kCh + off[k]];
-      return (uint32_t)(x0 + k - 1) < (uint32_t)W ? v : 0u;
-    };
-    auto load_g = [&](int yy, uint32_t (&e)[10]) {
-      const bool row = yy >= 0 && yy < H;  // the same for the whole wave
+  int xw = 0, x0 = 0;  // the wave's and the lane's first pixel of the piece
+  const int64_t pixels = (int64_t)N * H * W;
+  auto inside = [&](int k) { return (uint32_t)(x0 + k - 1) < (uint32_t)W; };
+  // K pixels of STRIDE bytes from pixel px + 8 half + (the lane's) more on,
+  // at the lane's byte `at`. Loads only: what lies outside the row is cleared
+  // where the values are used, so that a row's loads stay in flight while
+  // earlier rows are multiplied; only at the ends of the buffer are the
+  // addresses held inside it.
+  auto load = [&](const char* base, int64_t px, int more, int span, auto stride, uint32_t at,
+                  auto& e) {
+    constexpr int S = decltype(stride)::value, K = sizeof(e) / 4;
+    if (px >= 0 && px + span + 8 + K <= pixels) {  // the same for the whole wave
+      const char* p = base + px * S;
+      const uint32_t o = (uint32_t)(more + 8 * half) * S + at;
 #pragma unroll
-      for (int k = 0; k < 10; ++k) e[k] = row ? raw(g, yy, k) : 0u;
-    };
-    // a row of g at the three shifts: [0] pixels x0 - 1 .. (dx = 1), [1] x0
-    // .., [2] x0 + 1 ..
-    typedef bf16x8 Shifts[3];
-    auto shifts = [&](const uint32_t (&e)[10], Shifts& s) {
+      for (int k = 0; k < K; ++k) e[k] = *reinterpret_cast<const uint16_t*>(p + (o + k * S));
+    } else {
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
-        s[d] = frag(pair16(e[d], e[d + 1]), pair16(e[d + 2], e[d + 3]), pair16(e[d + 4], e[d + 5]),
-                    pair16(e[d + 6], e[d + 7]));
-    };
-    Shifts ga, gm, gz;  // rows y - 1, y, y + 1
-    uint32_t ex[8], eg[10];
-    // one row of x against the rows g0, g1 and g2 (filled here from its
-    // loads); the next row's loads go out ahead of the products
-    auto step = [&](Shifts& g0, Shifts& g1, Shifts& g2, bool more) {
-      shifts(eg, g2);
-      const bf16x8 a = frag(pair16(ex[0], ex[1]), pair16(ex[2], ex[3]), pair16(ex[4], ex[5]),
-                            pair16(ex[6], ex[7]));
-      if (more) {
-        load_g(y + 2, eg);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) ex[k] = raw(x, y + 1, k + 1);
+      for (int k = 0; k < K; ++k) {
+        const int64_t q = px + more + 8 * half + k;
+        e[k] = *reinterpret_cast<const uint16_t*>(
+            base + (q < 0 ? 0 : q < pixels ? q : pixels - 1) * S + at);
       }
-      // tap (dy, dx): x[y] meets g[y - dy] shifted by dx
+    }
+  };
+  auto load_g = [&](int yy, uint32_t (&e)[10]) {
+    load(g, img + (int64_t)yy * W + xw - 1, 0, 0, std::integral_constant<int, 2 * kCh>(), 2u * ch, e);
+  };
+  // x: 32 channels: row yy; 8 channels: the lane's row yy + ch / 8 - 1
+  const int dy = CIN == 32 ? 0 : ch < 24 ? ch >> 3 : 0;
+  auto load_x = [&](int yy, uint32_t (&e)[8]) {
+    load(x, img + (int64_t)(CIN == 32 ? yy : yy - 1) * W + xw, dy * W, CIN == 32 ? 0 : 2 * W,
+         std::integral_constant<int, 2 * CIN>(), 2u * (ch & (CIN - 1)), e);
+  };
+  // a row of g at the three shifts: [0] pixels x0 - 1 .. (dx = 1), [1] x0
+  // .., [2] x0 + 1 ..
+  typedef bf16x8 Shifts[3];
+  auto shifts = [&](int yy, const uint32_t (&e)[10], Shifts& s) {
+    const bool row = (uint32_t)yy < (uint32_t)H;
+    uint32_t v[10];
 #pragma unroll
-      for (int dx = -1; dx <= 1; ++dx) {
-        acc[dx + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g2[1 - dx], acc[dx + 1], 0, 0, 0);
-        acc[(dx + 4) % T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g1[1 - dx], acc[(dx + 4) % T], 0, 0, 0);
-        acc[(dx + 7) % T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g0[1 - dx], acc[(dx + 7) % T], 0, 0, 0);
+    for (int k = 0; k < 10; ++k) v[k] = row && inside(k) ? e[k] : 0u;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      s[d] = frag(pair16(v[d], v[d + 1]), pair16(v[d + 2], v[d + 3]), pair16(v[d + 4], v[d + 5]),
+                  pair16(v[d + 6], v[d + 7]));
+  };
+  auto rows_of_x = [&](int yy, const uint32_t (&e)[8]) {
+    const bool row = CIN == 32 || (ch < 24 && (uint32_t)(yy + (ch >> 3) - 1) < (uint32_t)H);
+    uint32_t v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = row && inside(k + 1) ? e[k] : 0u;
+    return frag(pair16(v[0], v[1]), pair16(v[2], v[3]), pair16(v[4], v[5]), pair16(v[6], v[7]));
+  };
+  auto bias = [&](const bf16x8& own) {  // row y, no shift
+    const uint4 o = __builtin_bit_cast(uint4, own);
+    const uint32_t ow[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      bacc += __builtin_bit_cast(float, ow[k] << 16) + __builtin_bit_cast(float, ow[k] & 0xFFFF0000u);
+  };
+  constexpr int D = CIN == 32 ? 2 : 3;  // rows in flight
+  for (int64_t s = pc.s0; s < pc.s1; ++colno, y = 0) {
+    const int64_t n = colno / pc.cols;
+    img = n * H * W;
+    xw = (int)(colno - n * pc.cols) * 16;
+    x0 = xw + 8 * half;
+    const int rows = (int)(pc.s1 - s < H - y ? pc.s1 - s : H - y);
+    WgradRow e[D];
+    if constexpr (CIN == 32) {
+      Shifts ga, gm, gz;  // rows y - 1, y, y + 1 of g
+      {
+        uint32_t u[10], v[10];
+        load_g(y - 1, u);
+        load_g(y, v);
+        load_g(y + 1, e[0].g);
+        load_x(y, e[0].x);
+        __builtin_amdgcn_sched_barrier(0);
+        shifts(y - 1, u, ga);
+        shifts(y, v, gm);
+        __builtin_amdgcn_sched_barrier(0);
+        load_g(y + 2, e[1].g);
+        load_x(y + 1, e[1].x);
       }
-      const uint4 own = __builtin_bit_cast(uint4, g1[1]);  // the bias: row y, no shift
-      const uint32_t ow[4] = {own.x, own.y, own.z, own.w};
+      // one row of x against the rows g0, g1 and g2 (filled here from its
+      // loads); the loads D rows ahead go out before the products
+      auto step = [&](Shifts& g0, Shifts& g1, Shifts& g2, WgradRow& w, bool more) {
+        __builtin_amdgcn_sched_barrier(0);
+        shifts(y + 1, w.g, g2);
+        const bf16x8 a = rows_of_x(y, w.x);
+        if (more) {
+          load_g(y + D + 1, w.g);
+          load_x(y + D, w.x);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // tap (dy, dx): x[y] meets g[y - dy] shifted by dx
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        bacc += __builtin_bit_cast(float, ow[k] << 16) +
-                __builtin_bit_cast(float, ow[k] & 0xFFFF0000u);
-      ++y;
-    };
-    for (int64_t s = pc.s0; s < pc.s1; ++colno, y = 0) {
-      const int64_t n = colno / pc.cols;
-      img = n * H * W;
-      x0 = (int)(colno - n * pc.cols) * 16 + 8 * half;
-      const int rows = (int)(pc.s1 - s < H - y ? pc.s1 - s : H - y);
-#pragma unroll
-      for (int k = 0; k < 10; ++k) off[k] = min(max(x0 + k - 1, 0), W - 1) * kCh + ch;
-      load_g(y - 1, eg);
-      shifts(eg, ga);
-      load_g(y, eg);
-      shifts(eg, gm);
-      load_g(y + 1, eg);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) ex[k] = raw(x, y, k + 1);
+        for (int dx = -1; dx <= 1; ++dx) {
+          acc[dx + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g2[1 - dx], acc[dx + 1], 0, 0, 0);
+          acc[(dx + 4) % T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g1[1 - dx], acc[(dx + 4) % T], 0, 0, 0);
+          acc[(dx + 7) % T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, g0[1 - dx], acc[(dx + 7) % T], 0, 0, 0);
+        }
+        bias(g1[1]);
+        ++y;
+      };
       for (int r = 0; r < rows;) {
-        step(ga, gm, gz, r + 1 < rows);
+        step(ga, gm, gz, e[0], r + D < rows);
         if (++r == rows) break;
-        step(gm, gz, ga, r + 1 < rows);
+        step(gm, gz, ga, e[1], r + D < rows);
         if (++r == rows) break;
-        step(gz, ga, gm, r + 1 < rows);
+        step(gz, ga, gm, e[0], r + D < rows);
+        if (++r == rows) break;
+        step(ga, gm, gz, e[1], r + D < rows);
+        if (++r == rows) break;
+        step(gm, gz, ga, e[0], r + D < rows);
+        if (++r == rows) break;
+        step(gz, ga, gm, e[1], r + D < rows);
         ++r;
       }
-      s += rows;
-    }
-  } else {
-    for (int64_t s = pc.s0; s < pc.s1; ++s, ++y) {
-      if (y == H) {
-        y = 0;
-        ++colno;
+    } else {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        load_g(y + d, e[d].g);
+        load_x(y + d, e[d].x);
       }
-      const int64_t n = colno / pc.cols;
-      img = n * H * W;
-      x0 = (int)(colno - n * pc.cols) * 16 + 8 * half;
-      uint32_t eb[8], ea[T][8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int px = x0 + k;
-        const uint32_t v = g[(img + (int64_t)y * W + min(px, W - 1)) * kCh + ch];
-        eb[k] = px < W ? v : 0u;
-      }
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const int tap = 4 * t + (ch >> 3), ci = ch & 7, yy = y + tap / 3 - 1, dx = tap % 3 - 1;
-        const bool row = tap < 9 && yy >= 0 && yy < H;
-        const int64_t base = (img + (int64_t)min(max(yy, 0), H - 1) * W) * CIN + ci;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int px = x0 + k + dx;
-          const uint32_t v = x[base + (int64_t)min(max(px, 0), W - 1) * CIN];
-          ea[t][k] = row && px >= 0 && px < W ? v : 0u;
+      auto step = [&](WgradRow& w, bool more) {
+        __builtin_amdgcn_sched_barrier(0);
+        Shifts gs;
+        shifts(y, w.g, gs);
+        const bf16x8 a = rows_of_x(y, w.x);
+        if (more) {
+          load_g(y + D, w.g);
+          load_x(y + D, w.x);
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int dx = -1; dx <= 1; ++dx)
+          acc[dx + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, gs[1 - dx], acc[dx + 1], 0, 0, 0);
+        bias(gs[1]);
+        ++y;
+      };
+      for (int r = 0; r < rows;) {
+        step(e[0], r + D < rows);
+        if (++r == rows) break;
+        step(e[1], r + D < rows);
+        if (++r == rows) break;
+        step(e[D - 1], r + D < rows);
+        ++r;
       }
-      const bf16x8 b = frag(pair16(eb[0], eb[1]), pair16(eb[2], eb[3]), pair16(eb[4], eb[5]),
-                            pair16(eb[6], eb[7]));
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            frag(pair16(ea[t][0], ea[t][1]), pair16(ea[t][2], ea[t][3]),
-                 pair16(ea[t][4], ea[t][5]), pair16(ea[t][6], ea[t][7])),
-            b, acc[t], 0, 0, 0);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) bacc += __builtin_bit_cast(float, eb[k] << 16);
     }
+    s += rows;
   }
-  wgrad_out<T>(acc, bacc, 9 * CIN, wgrad_smem, part + (int64_t)blockIdx.x * (9 * CIN * kCh + kCh));
+  wgrad_out<CIN, T>(acc, bacc, wgrad_smem, part + (int64_t)blockIdx.x * (9 * CIN * kCh + kCh));
 }
 
 // The parameters' update from the layers' partial sums, in one launch:

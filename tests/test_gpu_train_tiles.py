@@ -16,7 +16,8 @@ from oracle import upsampler as U
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1, 1), (1, 2, 3), (2, 5, 16), (1, 16, 17), (3, 7, 33), (2, 31, 32), (1, 3, 130),
-          (1, 130, 3), (5, 33, 49)]
+          (1, 130, 3), (5, 33, 49),
+          (3, 6500, 1), (2, 10100, 2)]  # ten rows and more to a wave
 
 
 @pytest.mark.parametrize("n,h,w", SHAPES)
