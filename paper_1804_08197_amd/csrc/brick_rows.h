@@ -80,6 +80,20 @@ __device__ __forceinline__ Vox4<T> load_row(const T* slot, const Row& w, int i, 
   }
   return o;
 }
+// Four voxels at p, at a row boundary of the slot, none beyond its end.
+template <typename T, bool MB>
+__device__ __forceinline__ Vox4<T> four_at(const T* p) {
+  Vox4<T> o;
+  if (sizeof(T) > 1 && MB) {
+    const uint2 ab = *reinterpret_cast<const uint2*>(p);
+    o.w[0] = ab.x;
+    o.w[sizeof(T) - 1] = ab.y;
+  } else {
+#pragma unroll
+    for (int k = 0; k < (int)sizeof(T); ++k) o.w[k] = reinterpret_cast<const uint32_t*>(p)[k];
+  }
+  return o;
+}
 template <typename T, bool MB>
 __device__ __forceinline__ void store_row(T* slot, const Row& w, int i, int S, int Sx,
                                           const Vox4<T>& o) {

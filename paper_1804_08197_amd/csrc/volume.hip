@@ -121,9 +121,13 @@ __global__ __launch_bounds__(256) void upload_kernel(uint8_t* __restrict__ pool,
 // per destination row of four voxels; a voxel's eight children lie in one
 // source brick (2g and 2g + 1 share a brick: its edge is even), whose slot
 // is one of the eight under the destination brick, and the child's offset
-// in the slot is a sum of one part per axis. Three levels of 512^3 uint16:
-// 226 us (400 with one thread, eight node look-ups and 64-bit divisions per
-// voxel); bound by the 2-byte loads, one per child.
+// in the slot is a sum of one part per axis. A stored row holds the core
+// voxels x - 1 .. x + 2: the children of the last three are read as whole
+// rows of four, those of the first (in the blocks before, maybe in another
+// brick) one by one, as are all of them at the level's far end. The row
+// beyond the core's end has one core voxel; the other three are apron.
+// Three levels of 512^3 uint16: 178 us (226 with a 2-byte load per child, 400
+// with one thread, eight node look-ups and 64-bit divisions per voxel).
 template <typename T, bool MB>
 __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t slot_bytes,
                                                          const int32_t* page, LevelGeom src,
@@ -166,8 +170,7 @@ __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t 
     const int r00 = fy(y0) + fz(z0), r10 = fy(y1) + fz(z0), r01 = fy(y0) + fz(z1),
               r11 = fy(y1) + fz(z1);
     Vox4<T> o{};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    auto one = [&](int k) {
       const int gx = min(b[0] * B + clampi(w.x + k - 1, 0, B - 1), dst.n[0] - 1);
       const int x0 = 2 * gx, x1 = min(2 * gx + 1, src.n[0] - 1);
       const T* p = slot_ptr<T>(pool, slot_bytes, slots[oct | ((x0 >> logB) & 1)]);
@@ -175,6 +178,34 @@ __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t 
       const uint32_t sum = (uint32_t)p[r00 + a] + p[r00 + c] + p[r10 + a] + p[r10 + c] +
                            p[r01 + a] + p[r01 + c] + p[r11 + a] + p[r11 + c];
       o.set(k, (sum + 4u) >> 3);
+    };
+    one(0);
+    const int cx = b[0] * B + w.x;  // voxels 1 .. 3 are the level's cx .. cx + 2
+    if (B >= 8 && w.x < B && 2 * cx + 5 < src.n[0]) {
+      const int h = (2 * w.x) & mask;  // their children: stored h + 1 .. h + 6
+      const T* p = slot_ptr<T>(pool, slot_bytes, slots[oct | (((2 * cx) >> logB) & 1)]) +
+                   (MB ? (h >> 2) << 6 : h);
+      const int next = MB ? 64 : 4;
+      const int rows[4] = {r00, r10, r01, r11};
+      Vox4<T> q[4][2];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) q[r][u] = four_at<T, MB>(p + rows[r] + u * next);
+      uint32_t s1 = 4u, s2 = 4u, s3 = 4u;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s1 += q[r][0].get(1) + q[r][0].get(2);
+        s2 += q[r][0].get(3) + q[r][1].get(0);
+        s3 += q[r][1].get(1) + q[r][1].get(2);
+      }
+      o.set(1, s1 >> 3);
+      o.set(2, s2 >> 3);
+      o.set(3, s3 >> 3);
+    } else if (w.x < B) {
+      one(1);
+      one(2);
+      one(3);
     }
     store_row<T, MB>(out, w, i, S, Sx, o);
   }
