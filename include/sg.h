@@ -393,7 +393,9 @@ sg_status sg_get_launch_config(const sg_volume *vol, sg_launch_config *config);
 /* Time launch configurations on this render (coordinate descent over the
  * five fields, two sweeps, each candidate timed over `repeats` renders after
  * one warm-up render, with events on hip_stream) and keep the fastest as the
- * volume's configuration. out_rgba receives the renders. best and best_ms
+ * volume's configuration. Short frames of the gather kernel put four lanes to
+ * a ray, a kernel the tile does not shape: its tile is timed with a lane to a
+ * ray, as larger frames run it. out_rgba receives the renders. best and best_ms
  * (either may be NULL) receive the choice and its time per render.
  * Synchronises hip_stream. SG_GATHER must be clear (the kernel is tuned). */
 sg_status sg_autotune(sg_volume *vol, int32_t n_views, const sg_view *views,

@@ -516,7 +516,7 @@ sg_status check_volume_ready(Volume* v) {
 sg_status render(sg_volume* vol, int32_t n_views, const sg_view* views,
                  const sg_render_params* params, float* const* out_rgba,
                  float* const* out_depth, sg_render_stats* stats, void* hip_stream,
-                 const int32_t* enable = nullptr) {
+                 const int32_t* enable = nullptr, bool may_split = true) {
   if (!vol) return fail(SG_ERR_INVALID_ARG, "volume is NULL");
   Volume* v = &vol->v;
   if (!params || !out_rgba) return fail(SG_ERR_INVALID_ARG, "params / out_rgba is NULL");
@@ -553,6 +553,7 @@ sg_status render(sg_volume* vol, int32_t n_views, const sg_view* views,
   fill_args(v, params, n_views, dv, v->cutmap, blocks, cfg, same_size(n_views, views),
             v->hit_tiles, &a);
   a.enable = enable;
+  if (!may_split) a.split = 0;
   const int C = v->d.channels;
   if (stats) {
     // micro-block bitmap: one bit per 4^3 block per (channel, level)
@@ -689,7 +690,12 @@ extern "C" sg_status sg_get_launch_config(const sg_volume* vol, sg_launch_config
 // staging differ), so the choice is by time alone: each candidate is timed
 // over `repeats` renders after one warm-up render, with events on the
 // caller's stream; a dimension's best value is kept before the next
-// dimension is tried, and the sweep runs twice.
+// dimension is tried, and the sweep runs twice. Four lanes to a ray run one
+// kernel whatever the tile (see raycast_plan), so there noise alone would
+// choose the tile, and frames with more tiles, which run the kernel that
+// uses it, would pay (a 32-pixel tile 0.135 ms for the upsampler's frame
+// where 8 and 16 take 0.096): the gather kernel's tiles are timed with a lane
+// to a ray.
 extern "C" sg_status sg_autotune(sg_volume* vol, int32_t n_views, const sg_view* views,
                                  const sg_render_params* params, float* const* out_rgba,
                                  int32_t repeats, sg_launch_config* best, double* best_ms,
@@ -710,14 +716,16 @@ extern "C" sg_status sg_autotune(sg_volume* vol, int32_t n_views, const sg_view*
   SG_HIP(hipEventCreate(&e0));
   SG_HIP(hipEventCreate(&e1));
   const LaunchConfig saved = v->cfg;
-  auto time_cfg = [&](const LaunchConfig& c, double* ms) -> sg_status {
+  auto time_cfg = [&](const LaunchConfig& c, double* ms, bool may_split = true) -> sg_status {
     v->cfg = c;
-    sg_status r = render(vol, n_views, views, params, out_rgba, nullptr, nullptr, s);
+    auto once = [&]() {
+      return render(vol, n_views, views, params, out_rgba, nullptr, nullptr, s, nullptr, may_split);
+    };
+    sg_status r = once();
     if (r != SG_OK) return r;
     SG_HIP(hipEventRecord(e0, s));
     for (int i = 0; i < repeats; ++i)
-      if ((r = render(vol, n_views, views, params, out_rgba, nullptr, nullptr, s)) != SG_OK)
-        return r;
+      if ((r = once()) != SG_OK) return r;
     SG_HIP(hipEventRecord(e1, s));
     SG_HIP(hipEventSynchronize(e1));
     float t = 0.f;
@@ -745,14 +753,21 @@ extern "C" sg_status sg_autotune(sg_volume* vol, int32_t n_views, const sg_view*
         if (std::memcmp(&c, &cur, sizeof(c)) == 0) continue;
         cand.push_back(c);
       }
+      const bool one_lane = dim == 1 && cur.gather && !cur.persistent;
+      double best_dim = cur_ms;
+      if (one_lane && (st = time_cfg(cur, &best_dim, false)) != SG_OK) break;
       for (const LaunchConfig& c : cand) {
         double ms = 0.0;
-        if ((st = time_cfg(c, &ms)) != SG_OK) break;
-        if (ms < cur_ms) {
+        if ((st = time_cfg(c, &ms, !one_lane)) != SG_OK) break;
+        if (ms < best_dim) {
           cur = c;
-          cur_ms = ms;
+          best_dim = ms;
         }
       }
+      if (!one_lane)
+        cur_ms = best_dim;
+      else if (st == SG_OK)
+        st = time_cfg(cur, &cur_ms);
     }
   }
   hipEventDestroy(e0);
