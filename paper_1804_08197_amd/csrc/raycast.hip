@@ -795,15 +795,21 @@ struct sg_render_graph {
   uint32_t* queue = nullptr;
   int tf_n = 0;
   double tf_lo[kMaxChannels]{}, tf_hi[kMaxChannels]{};
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
+  // the sequence with one lane to a ray, and with four where the rule can ask
+  // for them (see split_rays): which one a launch replays follows from the
+  // poses and tables of that launch
+  hipGraph_t graph[2] = {};
+  hipGraphExec_t exec[2] = {};
+  int64_t blocks = 0, tiles = 0;
 };
 
 namespace {
 
 void graph_free(sg_render_graph* g) {
-  if (g->exec) hipGraphExecDestroy(g->exec);
-  if (g->graph) hipGraphDestroy(g->graph);
+  for (int k = 0; k < 2; ++k) {
+    if (g->exec[k]) hipGraphExecDestroy(g->exec[k]);
+    if (g->graph[k]) hipGraphDestroy(g->graph[k]);
+  }
   if (g->dviews) hipFree(g->dviews);
   if (g->cutmap) hipFree(g->cutmap);
   if (g->queue) hipFree(g->queue);
@@ -821,6 +827,12 @@ sg_status add_node(hipGraph_t graph, Launch& l, hipGraphNode_t* dep, hipGraphNod
   kp.extra = nullptr;
   SG_HIP(hipGraphAddKernelNode(out, graph, dep, dep ? 1 : 0, &kp));
   return SG_OK;
+}
+
+// Four lanes to a ray for `tiles` tiles that meet the volume?
+bool graph_splits(const sg_render_graph* g, int64_t tiles) {
+  return split_rays(g->v, &g->params, g->cfg, ert_transmittance((float)g->params.ert_alpha),
+                    g->blocks, tiles);
 }
 
 }  // namespace
@@ -879,23 +891,30 @@ extern "C" sg_status sg_render_graph_create(sg_volume* vol, int32_t n_views,
                           (params->flags & SG_LOD) != 0, params->timepoint, g->cutmap,
                           &cut)) != SG_OK)
     return bail(st);
+  g->blocks = blocks;
+  g->tiles = hit_tiles(n_views, hv.data());
   RenderArgs a;
   fill_args(v, params, n_views, g->dviews, g->cutmap, blocks, cfg, same_size(n_views, views),
-            hit_tiles(n_views, hv.data()), &a);
+            g->tiles, &a);
   a.queue = g->queue;
-  if ((st = raycast_launch(v, a, false, &ray)) != SG_OK) return bail(st);
-  if (hipGraphCreate(&g->graph, 0) != hipSuccess)
-    return bail(fail(SG_ERR_DEVICE, "sg_render_graph_create: hipGraphCreate failed"));
-  hipGraphNode_t n0 = nullptr, n1 = nullptr, n2 = nullptr;
-  if ((st = add_node(g->graph, cut, nullptr, &n0)) != SG_OK) return bail(st);
-  hipGraphNode_t last = n0;
-  if (cfg.persistent) {
-    if ((st = add_node(g->graph, reset, &last, &n1)) != SG_OK) return bail(st);
-    last = n1;
+  for (int k = 0; k < 2; ++k) {
+    if (k == 1 && !graph_splits(g, 0)) break;  // no pose ever asks for it
+    RenderArgs ak = a;
+    ak.split = k;
+    if ((st = raycast_launch(v, ak, false, &ray)) != SG_OK) return bail(st);
+    if (hipGraphCreate(&g->graph[k], 0) != hipSuccess)
+      return bail(fail(SG_ERR_DEVICE, "sg_render_graph_create: hipGraphCreate failed"));
+    hipGraphNode_t n0 = nullptr, n1 = nullptr, n2 = nullptr;
+    if ((st = add_node(g->graph[k], cut, nullptr, &n0)) != SG_OK) return bail(st);
+    hipGraphNode_t last = n0;
+    if (cfg.persistent) {
+      if ((st = add_node(g->graph[k], reset, &last, &n1)) != SG_OK) return bail(st);
+      last = n1;
+    }
+    if ((st = add_node(g->graph[k], ray, &last, &n2)) != SG_OK) return bail(st);
+    if (hipGraphInstantiate(&g->exec[k], g->graph[k], nullptr, nullptr, 0) != hipSuccess)
+      return bail(fail(SG_ERR_DEVICE, "sg_render_graph_create: hipGraphInstantiate failed"));
   }
-  if ((st = add_node(g->graph, ray, &last, &n2)) != SG_OK) return bail(st);
-  if (hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0) != hipSuccess)
-    return bail(fail(SG_ERR_DEVICE, "sg_render_graph_create: hipGraphInstantiate failed"));
   *out = g;
   return SG_OK;
 }
@@ -913,8 +932,10 @@ extern "C" sg_status sg_render_graph_set_views(sg_render_graph* g, const sg_view
   if (st != SG_OK) return st;
   DeviceGuard guard(g->v->d.device);
   if (!guard.ok) return fail(SG_ERR_DEVICE, "cannot select device");
-  return stage_to_device(g->v, hv.data(), (int64_t)sizeof(ViewDev) * g->n_views, g->dviews,
-                         (hipStream_t)hip_stream);
+  st = stage_to_device(g->v, hv.data(), (int64_t)sizeof(ViewDev) * g->n_views, g->dviews,
+                       (hipStream_t)hip_stream);
+  if (st == SG_OK) g->tiles = hit_tiles(g->n_views, hv.data());
+  return st;
 }
 
 extern "C" sg_status sg_render_graph_launch(sg_render_graph* g, void* hip_stream) {
@@ -931,7 +952,7 @@ extern "C" sg_status sg_render_graph_launch(sg_render_graph* g, void* hip_stream
   hipStream_t s = (hipStream_t)hip_stream;
   sg_status st = commit(v, s);
   if (st != SG_OK) return st;
-  SG_HIP(hipGraphLaunch(g->exec, s));
+  SG_HIP(hipGraphLaunch(g->exec[g->exec[1] && graph_splits(g, g->tiles) ? 1 : 0], s));
   return SG_OK;
 }
 
