@@ -393,6 +393,10 @@ sg_status sg_set_transfer_function(sg_volume* vol, int32_t channel, const float*
   v->tf_lo[channel] = domain_lo;
   v->tf_hi[channel] = domain_hi;
   v->tf_set[channel] = true;
+  if (channel == 0) {
+    v->tf_floor = rgba[3];
+    for (int32_t i = 1; i < n_entries; ++i) v->tf_floor = std::min(v->tf_floor, (double)rgba[4 * i + 3]);
+  }
   v->tf_dirty = true;
   return SG_OK;
 }

@@ -134,12 +134,24 @@ bool step_adds_up(double step) {
   return m == std::floor(m);
 }
 
-// The pixels whose rays may meet the volume box: the projections of its eight
+// The part of the volume box that a render's region of interest leaves (the
+// whole box where they share no more than a face).
+void kept_box(const Volume* v, const sg_render_params* p, double lo[3], double hi[3]) {
+  bool roi = p->roi_on != 0;
+  for (int i = 0; i < 3; ++i)
+    roi = roi && std::max(0.0, p->roi[i]) < std::min((double)v->d.dims[i], p->roi[i + 3]);
+  for (int i = 0; i < 3; ++i) {
+    lo[i] = roi ? std::max(0.0, p->roi[i]) : 0.0;
+    hi[i] = roi ? std::min((double)v->d.dims[i], p->roi[i + 3]) : (double)v->d.dims[i];
+  }
+}
+
+// The pixels whose rays may meet the kept box: the projections of its eight
 // corners, one pixel wider on each side; the whole image when the view has a
 // lens map, a corner is not in front of the eye (rays leave it along R (sx,
 // sy, -1)), or the view is too narrow or too skewed for that margin to cover
 // the rounding of a few FP64 operations.
-void hit_bounds(const Volume* v, ViewDev* o) {
+void hit_bounds(const Volume* v, const sg_render_params* params, ViewDev* o) {
   o->hit[0] = o->hit[2] = 0;
   o->hit[1] = o->W - 1;
   o->hit[3] = o->H - 1;
@@ -154,10 +166,12 @@ void hit_bounds(const Volume* v, ViewDev* o) {
   const double inv[9] = {c0 / det, (R[2] * R[7] - R[1] * R[8]) / det, (R[1] * R[5] - R[2] * R[4]) / det,
                          c1 / det, (R[0] * R[8] - R[2] * R[6]) / det, (R[2] * R[3] - R[0] * R[5]) / det,
                          c2 / det, (R[1] * R[6] - R[0] * R[7]) / det, (R[0] * R[4] - R[1] * R[3]) / det};
+  double box[2][3];
+  kept_box(v, params, box[0], box[1]);
   double lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY}, far = 0.0;
   for (int k = 0; k < 8; ++k) {
     double p[3], c[3];
-    for (int i = 0; i < 3; ++i) p[i] = (((k >> i) & 1) ? (double)v->d.dims[i] : 0.0) - o->e[i];
+    for (int i = 0; i < 3; ++i) p[i] = box[(k >> i) & 1][i] - o->e[i];
     for (int i = 0; i < 3; ++i) c[i] = inv[3 * i] * p[0] + inv[3 * i + 1] * p[1] + inv[3 * i + 2] * p[2];
     const double size = std::fabs(c[0]) + std::fabs(c[1]) + std::fabs(c[2]);
     const double eye = std::fabs(o->e[0]) + std::fabs(o->e[1]) + std::fabs(o->e[2]);
@@ -210,16 +224,36 @@ int64_t hit_tiles(int n_views, const ViewDev* views) {
 // A tile that misses the volume costs four waves' launch (0.6 ns more than in
 // the plain kernel): a 128^3 volume that fills 1500 tiles of an image takes
 // 57 us against 87 of 16384 tiles, 137 against 140 of 65536, 399 against 298
-// of 262144; images beyond 32768 tiles are left to the plain kernel.
+// of 262144; images beyond 32768 tiles, or 128 a sample of the chain, are
+// left to the plain kernel (a region of 10 voxels an edge in 64^3: 15625 tiles
+// 27 -> 35 us; one of 77 in 512^3 123 -> 75, or 28 -> 35 where it is opaque).
+// A ray is no longer than the box the region of interest leaves, and no
+// longer than it takes to terminate where every table entry has extinction:
+// setting it up and writing it then weigh more than its samples (512^3,
+// extinction 5 throughout, 15000 tiles: 42 us against 90). Every segment of a
+// ray is set up by all four lanes too, so small bricks reach the line earlier
+// (at twelve segments' samples), unless rays mostly step through empty ones:
+//   blobs, bricks of 4:  256^3 1024 tiles 351 -> 294 us, 2500 358 -> 402, 10000 507 -> 805
+//   blobs, bricks of 8:  512^3 4096 tiles 399 -> 374, 6400 417 -> 498, 18906 721 -> 1083
+//   blobs, bricks of 16: 512^3 6400 tiles 347 -> 346, 10000 424 -> 472
+//   blobs, bricks of 32: 512^3 10000 tiles 375 -> 354, 18906 516 -> 552
+//   opaque ball, bricks of 8: 512^3 4096 tiles 1291 -> 830, 10000 1218 -> 943
 bool split_rays(const Volume* v, const sg_render_params* p, const LaunchConfig& cfg, float t_ert,
                 int64_t blocks, int64_t tiles) {
   if (!cfg.gather || cfg.persistent || v->d.channels != 1 ||
       p->model != SG_MODEL_EMISSION_ABSORPTION || !step_adds_up(p->step_voxels) ||
       !(t_ert < 1.0f) || (blocks << (2 * cfg.bt_log)) > 32768)
     return false;
-  const double edge = (double)std::max(v->d.dims[0], std::max(v->d.dims[1], v->d.dims[2]));
-  const double chain = edge / (p->step_voxels * (double)((int64_t)1 << p->lod_bias));
-  return (double)tiles <= ((p->flags & SG_LOD) ? 4.0 : 16.0) * chain;
+  double lo[3], hi[3], edge = 0.0;
+  kept_box(v, p, lo, hi);
+  for (int i = 0; i < 3; ++i) edge = std::max(edge, hi[i] - lo[i]);
+  const double step = p->step_voxels * (double)((int64_t)1 << p->lod_bias);
+  double chain = edge / step;
+  if (v->tf_floor > 0.0 && t_ert > 0.0f)
+    chain = std::min(chain, 1.0 - std::log((double)t_ert) / (v->tf_floor * step));
+  chain = std::min(chain, 12.0 * v->B / p->step_voxels);
+  return (double)tiles <= ((p->flags & SG_LOD) ? 4.0 : 16.0) * chain &&
+         (double)(blocks << (2 * cfg.bt_log)) <= 128.0 * chain;
 }
 
 // Arguments shared by the stream path and the graph path.
@@ -454,7 +488,7 @@ sg_status build_views_into(const Volume* v, int n_views, const sg_view* views,
     o.nsamp = nsamp ? nsamp[i] : nullptr;
     o.limit = w.ray_limit;
     o.tile_any = w.tile_any;
-    hit_bounds(v, &o);
+    hit_bounds(v, p, &o);
     if (blocks > (1 << 24)) return fail(SG_ERR_INVALID_ARG, "too many pixels in one call");
   }
   *total_blocks = blocks;

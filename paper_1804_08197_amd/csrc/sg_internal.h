@@ -116,8 +116,9 @@ struct ViewDev {
   double lens[4];      // k1, k2, cx, cy
   int32_t lens_on;
   uint8_t* tile_any;   // per 8x8-pixel block content flag or NULL
-  // pixels [x0, x1] x [y0, y1] outside of which no ray meets the volume box
-  // (the whole image where no such bound is known)
+  // pixels [x0, x1] x [y0, y1] outside of which no ray meets the volume box,
+  // or the region of interest in it (the whole image where no such bound is
+  // known)
   int32_t hit[4];
 };
 // May the ray of pixel (px, py) meet the volume box?
@@ -183,6 +184,7 @@ struct Volume {
   float* tf = nullptr;        // [C][tf_n + 1][4] (last entry repeated)
   int tf_n = 0;
   std::vector<float> tf_host[kMaxChannels];
+  double tf_floor = 0.0;      // the smallest extinction of the first channel's entries
   double tf_lo[kMaxChannels]{}, tf_hi[kMaxChannels]{};
   bool tf_set[kMaxChannels]{};
   bool tf_dirty = true;
