@@ -75,3 +75,18 @@ def bracket_error(gpu_rgba, refs):
     best = errs.min(axis=0)
     needed = int(((errs[0] > TOL) & (best <= TOL)).sum())
     return best, needed
+
+
+def median_us(run, repeats=9, inner=4):
+    """Median time of a call on the current stream, in us."""
+    import torch
+    us = []
+    for _ in range(repeats):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(inner):
+            run()
+        b.record()
+        torch.cuda.synchronize()
+        us.append(a.elapsed_time(b) * 1e3 / inner)
+    return float(np.median(us))

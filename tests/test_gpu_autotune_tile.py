@@ -1,27 +1,12 @@
 """The autotuner's tile where four lanes share a ray: such a frame runs one
 kernel whatever the tile, so the tile has to be chosen on the kernel that
 larger frames of the same program run, and must suit them."""
-import numpy as np
 import pytest
 
 import gen
-from tests.helpers import gpu_volume
+from tests.helpers import gpu_volume, median_us
 
 pytestmark = pytest.mark.gpu
-
-
-def median_us(run, repeats=9, inner=4):
-    import torch
-    us = []
-    for _ in range(repeats):
-        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-        a.record()
-        for _ in range(inner):
-            run()
-        b.record()
-        torch.cuda.synchronize()
-        us.append(a.elapsed_time(b) * 1e3 / inner)
-    return float(np.median(us))
 
 
 def test_tile_tuned_on_a_short_frame_suits_a_long_one():

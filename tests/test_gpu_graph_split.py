@@ -6,23 +6,9 @@ import numpy as np
 import pytest
 
 import gen
-from tests.helpers import gpu_volume
+from tests.helpers import gpu_volume, median_us
 
 pytestmark = pytest.mark.gpu
-
-
-def median_us(run, repeats=9, inner=4):
-    import torch
-    us = []
-    for _ in range(repeats):
-        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-        a.record()
-        for _ in range(inner):
-            run()
-        b.record()
-        torch.cuda.synchronize()
-        us.append(a.elapsed_time(b) * 1e3 / inner)
-    return float(np.median(us))
 
 
 # 64^3 filling two images: 32768 tiles, far beyond the limit of its 128 samples

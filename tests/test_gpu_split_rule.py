@@ -7,8 +7,7 @@ import numpy as np
 import pytest
 
 import gen
-from tests.helpers import gpu_volume
-from tests.test_gpu_graph_split import median_us
+from tests.helpers import gpu_volume, median_us
 from tests.test_gpu_split_rays import CENTRE, same, view, volume
 
 pytestmark = pytest.mark.gpu
