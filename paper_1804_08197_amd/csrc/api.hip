@@ -208,10 +208,10 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
   }
   if (v->cache) v->req_list = v->req_count + kReqHead;
   // the block maxima (1/64 or 1/32 of the pool) only speed renders up: a
-  // volume that leaves no room for them goes without
+  // volume that leaves no room for them goes without, as do small bricks
   v->bmax_stride = v->slot_bytes >> bmax_shift(v->M != 0);
   const int64_t bmax_bytes = v->slots * v->bmax_stride;
-  if (v->bmax_stride >= (int64_t)v->Mb * v->Mb * v->Mb * v->bpv &&
+  if (dark_regions(v->Mb) > 1 && v->bmax_stride >= (int64_t)v->Mb * v->Mb * v->Mb * v->bpv &&
       hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
       (uint64_t)bmax_bytes + ((uint64_t)1 << 30) < free_b) {
     if (hipMalloc((void**)&v->bmax, (size_t)bmax_bytes) == hipSuccess) {

@@ -139,24 +139,20 @@ __device__ __forceinline__ void row_range(const Vox4<T>& o, int left, uint32_t& 
 }
 
 // A workgroup's (256 threads) share of a brick's value range, into range[0]
-// (minimum) and range[1] (maximum), and of the smallest maximum of its
-// blocks, into *dark: stored when the workgroup holds the whole brick, else
-// merged with atomics (they start at ~0, 0 and ~0; minima and maxima do not
-// depend on the order).
-__device__ __forceinline__ void range_out(uint32_t lo, uint32_t hi, uint32_t dk, uint32_t* range,
-                                          uint32_t* dark, bool whole) {
+// (minimum) and range[1] (maximum): stored when the workgroup holds the whole
+// brick, else merged with atomics (they start at ~0 and 0; minima and maxima
+// do not depend on the order).
+__device__ __forceinline__ void range_out(uint32_t lo, uint32_t hi, uint32_t* range, bool whole) {
 #pragma unroll
   for (int m = 32; m > 0; m >>= 1) {
     lo = min(lo, (uint32_t)__shfl_xor((int)lo, m));
     hi = max(hi, (uint32_t)__shfl_xor((int)hi, m));
-    dk = min(dk, (uint32_t)__shfl_xor((int)dk, m));
   }
-  __shared__ uint32_t part[3][4];
+  __shared__ uint32_t part[2][4];
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
     part[0][wave] = lo;
     part[1][wave] = hi;
-    part[2][wave] = dk;
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
@@ -164,16 +160,13 @@ __device__ __forceinline__ void range_out(uint32_t lo, uint32_t hi, uint32_t dk,
   for (int k = 1; k < 4; ++k) {
     lo = min(lo, part[0][k]);
     hi = max(hi, part[1][k]);
-    dk = min(dk, part[2][k]);
   }
   if (whole) {
     range[0] = lo;
     range[1] = hi;
-    *dark = dk;
   } else {
     atomicMin(range, lo);
     atomicMax(range + 1, hi);
-    atomicMin(dark, dk);
   }
 }
 

@@ -34,8 +34,7 @@ template <typename T, bool MB, bool WIDE>
 __global__ __launch_bounds__(256) void put_kernel(uint8_t* __restrict__ pool, int64_t slot_bytes,
                                                   const int32_t* slots, const int32_t* entries,
                                                   const T* __restrict__ src, uint32_t* range,
-                                                  uint32_t* dark, uint8_t* bmax,
-                                                  int64_t bmax_stride, int per,
+                                                  uint8_t* bmax, int64_t bmax_stride, int per,
                                                   int S, int Sx, int M) {
   const int64_t j = blockIdx.x / (unsigned)per;
   const int part = (int)(blockIdx.x % (unsigned)per), items = M * M * M * 16;
@@ -44,7 +43,7 @@ __global__ __launch_bounds__(256) void put_kernel(uint8_t* __restrict__ pool, in
   T* dst = reinterpret_cast<T*>(pool + (int64_t)slot * slot_bytes);
   T* bm = bmax ? reinterpret_cast<T*>(bmax + (int64_t)slot * bmax_stride) : nullptr;
   src += j * (int64_t)S * S * S;
-  uint32_t lo = 0xFFFFFFFFu, hi = 0u, dk = 0xFFFFFFFFu;
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   // (the same trip count for every lane: blocks are folded across lanes)
   for (int i0 = part * 256 * kRowBatch; i0 < items; i0 += per * 256 * kRowBatch) {
     Row w[kRowBatch];
@@ -78,25 +77,23 @@ __global__ __launch_bounds__(256) void put_kernel(uint8_t* __restrict__ pool, in
       }
       hi = max(hi, rmax);
       rmax = row16_max(rmax);
-      if (i < items) dk = min(dk, rmax);
       if (bm && i < items && (i & 15) == 0) bm[i >> 4] = (T)rmax;
     }
   }
-  range_out(lo, hi, dk, range + 2 * (int64_t)entries[j], dark + entries[j], per == 1);
+  range_out(lo, hi, range + 2 * (int64_t)entries[j], per == 1);
 }
 
 // The small tables of a put: a freshly stored brick counts as used now
 // (stamp), its range starts empty, and the page table takes its new entries.
 __global__ void put_tables_kernel(uint32_t* stamp, const int32_t* slots, const int32_t* entries,
-                                  int n, uint32_t frame, uint32_t* range, uint32_t* dark,
-                                  int32_t* page, const int32_t* idx, const int32_t* val, int np) {
+                                  int n, uint32_t frame, uint32_t* range, int32_t* page,
+                                  const int32_t* idx, const int32_t* val, int np) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
     stamp[slots[i]] = frame;
     const int64_t e = entries[i];
     range[2 * e] = 0xFFFFFFFFu;
     range[2 * e + 1] = 0u;
-    dark[e] = 0xFFFFFFFFu;
   }
   if (i < np) page[idx[i]] = val[i];
 }
@@ -215,8 +212,8 @@ void launch_put(Volume* v, int n, const int32_t* d_slot, const int32_t* d_ent, c
   const bool wide = v->bpv == 2 && reinterpret_cast<uintptr_t>(dsrc) % 4 == 0;
 #define SG_PUT(T, MB, WIDE)                                                                    \
   hipLaunchKernelGGL((put_kernel<T, MB, WIDE>), grid, dim3(256), 0, s, v->pool, v->slot_bytes, \
-                     d_slot, d_ent, (const T*)dsrc, v->range, v->dark, v->bmax, v->bmax_stride, per,    \
-                     v->S, v->Sx, v->Mb)
+                     d_slot, d_ent, (const T*)dsrc, v->range, v->bmax, v->bmax_stride, per, v->S,     \
+                     v->Sx, v->Mb)
   if (v->bpv == 1) {
     if (v->M) SG_PUT(uint8_t, true, false); else SG_PUT(uint8_t, false, false);
   } else if (wide) {
@@ -225,6 +222,7 @@ void launch_put(Volume* v, int n, const int32_t* d_slot, const int32_t* d_ent, c
     if (v->M) SG_PUT(uint16_t, true, false); else SG_PUT(uint16_t, false, false);
   }
 #undef SG_PUT
+  launch_dark(v, n, d_slot, d_ent, v->dark, s);
 }
 
 // Both put entry points: the regions come from one buffer (src, host or
@@ -367,8 +365,8 @@ sg_status put_impl(sg_volume* vol, int32_t channel, int32_t timepoint, int32_t l
     if (b0 + k == n) SG_HIP(hipEventRecord(v->put_copied, s));
     if (b0 == 0)
       hipLaunchKernelGGL(put_tables_kernel, dim3((unsigned)((std::max(n, np) + 255) / 256)),
-                         dim3(256), 0, s, v->stamp, d_slot, d_ent, n, v->frame, v->range, v->dark,
-                         v->page, d_pidx, d_pval, np);
+                         dim3(256), 0, s, v->stamp, d_slot, d_ent, n, v->frame, v->range, v->page,
+                         d_pidx, d_pval, np);
     launch_put(v, (int)k, d_slot + b0, d_ent + b0, dsrc, s);
     SG_HIP(hipGetLastError());
   }

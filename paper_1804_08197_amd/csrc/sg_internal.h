@@ -151,6 +151,10 @@ __host__ __device__ __forceinline__ int64_t slot_index(int x, int y, int z, int 
 // of Volume::bmax: Mb^3 voxels in 1/64 of a micro-block slot (Mb^3 blocks of
 // 64 voxels), in 1/32 of a linear one (S^3 voxels and padding; Mb = ceil(S / 4)).
 __host__ __device__ constexpr int bmax_shift(bool micro) { return micro ? 6 : 5; }
+// Regions to an edge of a slot of Mb blocks an edge that are looked at
+// together before slabs are tested (one: the brick, which is skipped as a
+// whole where it holds nothing).
+__host__ __device__ constexpr int dark_regions(int Mb) { return Mb < 5 ? 1 : (Mb + 1) / 3; }
 
 struct Volume {
   sg_volume_desc d{};
@@ -175,11 +179,12 @@ struct Volume {
   uint8_t* bmax = nullptr;    // [slots][Mb^3] largest voxel of each 4^3 block
                               // of a slot (blocks x fastest), or NULL
   int64_t bmax_stride = 0;    // bytes per slot of bmax (slot_bytes >> bmax_shift)
-  uint32_t* dark = nullptr;   // [T][C][nodes] smallest of a brick's block maxima
+  uint32_t* dark = nullptr;   // [T][C][nodes] what a quarter of a brick's
+                              // regions stay at or below (see dark_kernel)
   uint8_t* empty = nullptr;   // [T][nodes] bit 0: every channel transparent,
                               // bit 1: every channel emits nothing, bits 2
-                              // and 3: no 4^3 block of some channel is
-                              // transparent (emits nothing)
+                              // and 3: few regions of some channel are
+                              // transparent (emit nothing)
   NodeInfo* info = nullptr;   // [nodes]
   float* tf = nullptr;        // [C][tf_n + 1][4] (last entry repeated)
   int tf_n = 0;
@@ -272,6 +277,10 @@ sg_status launch_downsample(Volume* v, int c, int t, int level_dst,
                             hipStream_t s);
 // Aprons, block maxima and value ranges of one (channel, timepoint).
 sg_status launch_commit(Volume* v, int c, int t, hipStream_t s);
+// Volume::dark of n bricks from their block maxima, at dark[entries[j]]
+// (entries NULL: dark[j]).
+void launch_dark(Volume* v, int n, const int32_t* slots, const int32_t* entries, uint32_t* dark,
+                 hipStream_t s);
 sg_status launch_empty(Volume* v, hipStream_t s);
 // Byte offsets in Volume::tf of what follows the tables: the domains, the
 // skip flags' tables (see empty_kernel), RenderArgs::dim.

@@ -1,0 +1,74 @@
+"""A node with hardly any empty space pays for no test of its slabs: a frame
+of a volume with opaque blocks scattered everywhere takes as long with the
+skips as without, and gives the same image. Brick sizes, slot layouts and
+stored types at which the regions that decide it are cut differently give the
+same image too, whatever the share of empty space."""
+import numpy as np
+import pytest
+
+import gen
+from tests.helpers import LAYOUT_IDS, LAYOUTS, gpu_volume, median_us
+
+pytestmark = pytest.mark.gpu
+
+
+def scattered(n, share, dtype=np.uint16):
+    m = -(-n // 4)
+    on = np.random.default_rng(4).random((m, m, m)) < share
+    on = np.kron(on, np.ones((4, 4, 4), dtype=bool))[:n, :n, :n]
+    return np.where(on, 36 if dtype == np.uint8 else 9200, 0 if dtype == np.uint8 else 200).astype(dtype)
+
+
+def hot(top):
+    k = np.arange(256) / 255
+    return np.stack([k, k, k, np.where(k < 5 / 255, 0, top * k)], 1)
+
+
+@pytest.mark.parametrize("share", [0.1, 0.5])
+@pytest.mark.parametrize("layout", LAYOUTS, ids=LAYOUT_IDS)
+def test_scattered_blocks_cost_no_tests(layout, share):
+    import torch
+
+    from paper_1804_08197_amd import sg
+    n = 512
+    on = torch.rand(n // 4, n // 4, n // 4, device="cuda",
+                    generator=torch.Generator("cuda").manual_seed(4)) < share
+    vol = (200 + 9000 * on.to(torch.int32)).to(torch.uint16)
+    for a in range(3):
+        vol = vol.repeat_interleave(4, a)
+    h = gpu_volume([vol.cpu().numpy()], 64, 4, [hot(0.05)], [(0, 65535)], layout=layout)
+    try:
+        eye = np.array((1.0, 0.7, 0.4)) * 1.25 * n / 1.285 + n / 2
+        v = gen.view(gen.look_at(eye, (n / 2, n / 2, n / 2)), 1080, 1200, np.tan(np.radians(50)))
+        img = [torch.empty(1200, 1080, 4, device="cuda") for _ in range(2)]
+        sides = [lambda s=s: sg.sg_render_views(h, [v], {"skip_empty": s}, [img[s]]) for s in (0, 1)]
+        us = [median_us(s) for s in sides * 3]
+        print(share, us, flush=True)
+        assert min(us[1::2]) <= 1.03 * min(us[0::2]), us
+        assert torch.equal(*img)
+    finally:
+        sg.sg_volume_destroy(h)
+
+
+@pytest.mark.parametrize("layout", LAYOUTS, ids=LAYOUT_IDS)
+@pytest.mark.parametrize("dtype", [np.uint8, np.uint16])
+@pytest.mark.parametrize("brick", [2, 8, 16, 32, 64, 128, 256])
+def test_same_image_at_every_brick(brick, dtype, layout):
+    import torch
+
+    from paper_1804_08197_amd import sg
+    n, top = 70 if brick > 2 else 24, np.iinfo(dtype).max
+    vol = scattered(n, 0.02, dtype)
+    vol[:, n // 3:, :] = 0  # a quiet part, a scattered one and a full one
+    vol[: n // 4] = top // 3
+    h = gpu_volume([vol], brick, 1 if brick == 256 else 2, [hot(0.3)], [(0, top)], layout=layout)
+    try:
+        v = gen.view(gen.look_at((1.6 * n, 1.3 * n, n), (n / 2, n / 2, n / 2)), 150, 130, 0.6)
+        for model in ("ea", "eo"):
+            img = [torch.full((130, 150, 4), float("nan"), device="cuda") for _ in range(2)]
+            for s in (0, 1):
+                sg.sg_render_views(h, [v], {"lod": 0, "skip_empty": s, "model": model}, [img[s]])
+            torch.cuda.synchronize()
+            assert torch.isfinite(img[0]).all() and torch.equal(*img)
+    finally:
+        sg.sg_volume_destroy(h)
