@@ -341,31 +341,34 @@ __global__ __launch_bounds__(256) void range_kernel(const uint8_t* __restrict__ 
 // more than the slabs stepped over save (every fiftieth 4^3 block opaque, at
 // random, and a quarter of the regions free of them: 1431 us a frame without
 // asking, 1419 with; every tenth, none free: 1421 and 1544). One workgroup
-// per brick. Bound by latency: the block maxima are read once, all loads
+// per brick, or one wave for bricks of 16 and 32 (37449 of 16: 27 us; 145 with a
+// workgroup). Bound by latency: the block maxima are read once, all loads
 // together, and folded into the regions' in LDS; one wave searches them, a
 // ballot for every 64, without barriers.
 template <typename T>
 __global__ __launch_bounds__(256) void dark_kernel(const uint8_t* bmax, int64_t bmax_stride,
                                                    const int32_t* slots, const int32_t* entries,
-                                                   int M, uint32_t* dark) {
-  constexpr int kMost = 22 * 22 * 22;  // bricks of 256: 65 blocks an edge
-  __shared__ uint32_t top[kMost];
-  const T* bm = reinterpret_cast<const T*>(bmax + (int64_t)slots[blockIdx.x] * bmax_stride);
+                                                   int count, int threads, int M, uint32_t* dark) {
+  extern __shared__ uint32_t dark_smem[];  // the regions of each of the workgroup's bricks
+  const int sub = (int)threadIdx.x / threads, tid = (int)threadIdx.x % threads;
+  const int j = (int)blockIdx.x * (256 / threads) + sub;
+  const T* bm = reinterpret_cast<const T*>(bmax + (int64_t)slots[min(j, count - 1)] * bmax_stride);
   const uint32_t* words = reinterpret_cast<const uint32_t*>(bm);  // (4-byte aligned, as is their end)
   constexpr int kPer = 4 / (int)sizeof(T), kLoads = 20 / kPer;    // a brick of 64: one round
   const int G = dark_regions(M), n = G * G * G, blocks = M * M * M, nw = (blocks + kPer - 1) / kPer;
   const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_mm = __builtin_amdgcn_rcpf((float)(M * M));
-  for (int r = threadIdx.x; r < n; r += 256) top[r] = 0u;
+  uint32_t* const top = dark_smem + sub * n;
+  for (int r = tid; r < n; r += threads) top[r] = 0u;
   __syncthreads();
-  for (int i0 = threadIdx.x; i0 < nw; i0 += 256 * kLoads) {
+  for (int i0 = tid; i0 < nw; i0 += threads * kLoads) {
     uint32_t w[kLoads];
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) w[u] = words[min(i0 + 256 * u, nw - 1)];
+    for (int u = 0; u < kLoads; ++u) w[u] = words[min(i0 + threads * u, nw - 1)];
 #pragma unroll
     for (int u = 0; u < kLoads; ++u)
 #pragma unroll
       for (int k = 0; k < kPer; ++k) {
-        const int b = kPer * (i0 + 256 * u) + k;
+        const int b = kPer * (i0 + threads * u) + k;
         if (b >= blocks) continue;
         const int bz = quot_exact(b, inv_mm), t = b - bz * M * M, by = quot_exact(t, inv_m),
                   bx = t - by * M;
@@ -375,8 +378,8 @@ __global__ __launch_bounds__(256) void dark_kernel(const uint8_t* bmax, int64_t 
       }
   }
   __syncthreads();
-  if (threadIdx.x >= 64) return;
-  const int lane = threadIdx.x, need = (n + 3) / 4;
+  if (tid >= 64 || j >= count) return;  // whole waves
+  const int lane = tid, need = (n + 3) / 4;
   uint32_t v[4];  // the first 256 regions
 #pragma unroll
   for (int k = 0; k < 4; ++k) v[k] = lane + 64 * k < n ? top[lane + 64 * k] : 0xFFFFFFFFu;
@@ -389,7 +392,7 @@ __global__ __launch_bounds__(256) void dark_kernel(const uint8_t* bmax, int64_t 
     for (int r = 256; r < n; r += 64) c += __popcll(__ballot(r + lane < n && top[min(r + lane, n - 1)] <= mid));
     if (c >= need) hi = mid; else lo = mid + 1;
   }
-  if (lane == 0) dark[entries ? entries[blockIdx.x] : (int)blockIdx.x] = lo;
+  if (lane == 0) dark[entries ? entries[j] : j] = lo;
 }
 
 // Skip flags (one thread per (timepoint, node)). Bit 0 (transparent): for
@@ -535,12 +538,15 @@ sg_status launch_commit(Volume* v, int c, int t, hipStream_t s) {
 void launch_dark(Volume* v, int n, const int32_t* slots, const int32_t* entries, uint32_t* dark,
                  hipStream_t s) {
   if (!v->bmax) return;  // slabs are not tested
+  const int G = dark_regions(v->Mb), threads = v->Mb <= 9 ? 64 : 256, bricks = 256 / threads;
+  const dim3 grid((unsigned)((n + bricks - 1) / bricks));
+  const size_t lds = (size_t)bricks * G * G * G * 4;  // 42592 bytes at most (bricks of 256)
   if (v->bpv == 1)
-    hipLaunchKernelGGL(dark_kernel<uint8_t>, dim3((unsigned)n), dim3(256), 0, s, v->bmax,
-                       v->bmax_stride, slots, entries, v->Mb, dark);
+    hipLaunchKernelGGL(dark_kernel<uint8_t>, grid, dim3(256), lds, s, v->bmax, v->bmax_stride,
+                       slots, entries, n, threads, v->Mb, dark);
   else
-    hipLaunchKernelGGL(dark_kernel<uint16_t>, dim3((unsigned)n), dim3(256), 0, s, v->bmax,
-                       v->bmax_stride, slots, entries, v->Mb, dark);
+    hipLaunchKernelGGL(dark_kernel<uint16_t>, grid, dim3(256), lds, s, v->bmax, v->bmax_stride,
+                       slots, entries, n, threads, v->Mb, dark);
 }
 
 // The largest voxel value whose table index fma(x, scale, bias) is at most
