@@ -55,6 +55,65 @@ struct Vox4 {
 // chip, which measured 1.5 to 2 TB/s).
 constexpr int kRowBatch = 4;
 
+// Workgroups per brick for `bricks` bricks of `items` rows: enough for
+// about 4096 workgroups in all (16 per CU), each with at least one batch
+// of rows per thread, and one per brick (no merging of ranges) from 4096
+// bricks on.
+inline int groups_per_brick(int64_t bricks, int items) {
+  const int64_t want = (4096 + bricks - 1) / std::max<int64_t>(bricks, 1);
+  const int64_t most = std::max<int64_t>(1, items / (256 * kRowBatch));
+  return (int)std::max<int64_t>(1, std::min(want, most));
+}
+
+// The workgroups (256 threads) of a launch over n bricks of M blocks an edge:
+// `per` to a brick, or `pack`: bricks of 2 and 4 (M = 1 and 2) share
+// workgroups, one row to a thread: all 16 and 128 rows, or the 4 and 32 that
+// hold core voxels (`core`). With a workgroup each, most of its threads had
+// nothing to do, and a 256^3 volume in bricks of 4 took 437, 66 and 667 us to
+// upload, build and commit (343, 44 and 499 with one thread per voxel; 316, 43
+// and 384 so).
+struct Shares {
+  bool pack;
+  int per, n;
+  unsigned grid;
+};
+__host__ __device__ constexpr int pack_log(int M, bool core) {  // log2 threads to a brick
+  return M == 1 ? (core ? 2 : 4) : (core ? 5 : 7);
+}
+inline Shares brick_shares(int64_t n, int M, bool core = false) {
+  Shares s;
+  s.n = (int)n;
+  s.pack = M <= 2;
+  s.per = s.pack ? 1 : groups_per_brick(n, M * M * M * 16);
+  s.grid = (unsigned)(s.pack ? ((n << pack_log(M, core)) + 255) / 256 : n * s.per);
+  return s;
+}
+// A thread's part in such a launch: brick j (at or beyond n: none), workgroup
+// `part` of those that share it, thread `lane` of `threads` on the brick, and
+// which of the workgroup's bricks it is.
+struct Part {
+  int64_t j;
+  int part, lane, threads, sub;
+};
+template <bool PACK, bool CORE = false>
+__device__ __forceinline__ Part brick_part(int per, int M) {
+  if (PACK) {
+    const int log = pack_log(M, CORE), sub = (int)(threadIdx.x >> log);
+    return Part{((int64_t)blockIdx.x << (8 - log)) + sub, 0, (int)(threadIdx.x & ((1u << log) - 1)),
+                1 << log, sub};
+  }
+  return Part{(int64_t)(blockIdx.x / (unsigned)per), (int)(blockIdx.x % (unsigned)per),
+              (int)threadIdx.x, 256, 0};
+}
+template <bool PACK, bool CORE = false>
+constexpr int kMostBricks = PACK ? 256 >> pack_log(1, CORE) : 1;  // to a workgroup
+// Row k of those of a brick of 2 or 4 that hold core voxels: its number among
+// all rows.
+__device__ __forceinline__ int core_row_number(int k, int M) {
+  const int bx = k & (M - 1), t = k >> (M - 1), y = 1 + (t & (2 * M - 1)), z = 1 + (t >> M);
+  return 16 * (((z >> 2) * M + (y >> 2)) * M + bx) + 4 * (z & 3) + (y & 3);
+}
+
 // Element offset of a row's first voxel in the slot.
 template <bool MB>
 __device__ __forceinline__ int64_t row_offset(const Row& w, int i, int S, int Sx) {
@@ -141,8 +200,20 @@ __device__ __forceinline__ void row_range(const Vox4<T>& o, int left, uint32_t& 
 // A workgroup's (256 threads) share of a brick's value range, into range[0]
 // (minimum) and range[1] (maximum): stored when the workgroup holds the whole
 // brick, else merged with atomics (they start at ~0 and 0; minima and maxima
-// do not depend on the order).
-__device__ __forceinline__ void range_out(uint32_t lo, uint32_t hi, uint32_t* range, bool whole) {
+// do not depend on the order). With PACK every brick of the workgroup is
+// whole: range is the thread's own brick's, NULL beyond the last.
+template <bool PACK>
+__device__ __forceinline__ void range_out(uint32_t lo, uint32_t hi, uint32_t* range, bool whole,
+                                          const Part& p) {
+  if (PACK && p.threads == 16) {  // the same for the whole workgroup
+    hi = row16_max(hi);
+    lo = ~row16_max(~lo);
+    if (p.lane == 0 && range) {
+      range[0] = lo;
+      range[1] = hi;
+    }
+    return;
+  }
 #pragma unroll
   for (int m = 32; m > 0; m >>= 1) {
     lo = min(lo, (uint32_t)__shfl_xor((int)lo, m));
@@ -155,6 +226,12 @@ __device__ __forceinline__ void range_out(uint32_t lo, uint32_t hi, uint32_t* ra
     part[1][wave] = hi;
   }
   __syncthreads();
+  if (PACK) {  // two waves a brick
+    if (p.lane != 0 || !range) return;
+    range[0] = min(part[0][wave], part[0][wave + 1]);
+    range[1] = max(part[1][wave], part[1][wave + 1]);
+    return;
+  }
   if (threadIdx.x != 0) return;
 #pragma unroll
   for (int k = 1; k < 4; ++k) {
@@ -168,16 +245,6 @@ __device__ __forceinline__ void range_out(uint32_t lo, uint32_t hi, uint32_t* ra
     atomicMin(range, lo);
     atomicMax(range + 1, hi);
   }
-}
-
-// Workgroups per brick for `bricks` bricks of `items` rows: enough for
-// about 4096 workgroups in all (16 per CU), each with at least one batch
-// of rows per thread, and one per brick (no merging of ranges) from 4096
-// bricks on.
-inline int groups_per_brick(int64_t bricks, int items) {
-  const int64_t want = (4096 + bricks - 1) / std::max<int64_t>(bricks, 1);
-  const int64_t most = std::max<int64_t>(1, items / (256 * kRowBatch));
-  return (int)std::max<int64_t>(1, std::min(want, most));
 }
 
 }  // namespace sg

@@ -30,14 +30,17 @@ namespace {
 // of 64^3 uint16 per put: 28 us on average (61 + 344 us when storing and
 // taking the ranges were two kernels, with 64-bit divisions per voxel and
 // one workgroup per brick).
-template <typename T, bool MB, bool WIDE>
+template <typename T, bool MB, bool WIDE, bool PACK>
 __global__ __launch_bounds__(256) void put_kernel(uint8_t* __restrict__ pool, int64_t slot_bytes,
                                                   const int32_t* slots, const int32_t* entries,
                                                   const T* __restrict__ src, uint32_t* range,
-                                                  uint8_t* bmax, int64_t bmax_stride, int per,
-                                                  int S, int Sx, int M) {
-  const int64_t j = blockIdx.x / (unsigned)per;
-  const int part = (int)(blockIdx.x % (unsigned)per), items = M * M * M * 16;
+                                                  uint8_t* bmax, int64_t bmax_stride, int n,
+                                                  int per, int S, int Sx, int M) {
+  constexpr int kBatch = PACK ? 1 : kRowBatch;
+  const int items = M * M * M * 16;
+  const Part p = brick_part<PACK>(per, M);
+  const bool any = !PACK || p.j < n;
+  const int64_t j = any ? p.j : 0;
   const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_mm = __builtin_amdgcn_rcpf((float)(M * M));
   const int32_t slot = slots[j];
   T* dst = reinterpret_cast<T*>(pool + (int64_t)slot * slot_bytes);
@@ -45,42 +48,43 @@ __global__ __launch_bounds__(256) void put_kernel(uint8_t* __restrict__ pool, in
   src += j * (int64_t)S * S * S;
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   // (the same trip count for every lane: blocks are folded across lanes)
-  for (int i0 = part * 256 * kRowBatch; i0 < items; i0 += per * 256 * kRowBatch) {
-    Row w[kRowBatch];
-    Vox4<T> o[kRowBatch];
-    bool on[kRowBatch];
+  for (int i0 = p.part * 256 * kBatch; i0 < items; i0 += per * 256 * kBatch) {
+    Row w[kBatch];
+    Vox4<T> o[kBatch];
+    bool on[kBatch];
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) {
-      const int i = i0 + 256 * u + (int)threadIdx.x;
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + 256 * u + p.lane;
       w[u] = row_at(i, M, inv_m, inv_mm);
-      on[u] = i < items && w[u].y < S && w[u].z < S;
+      on[u] = any && i < items && w[u].y < S && w[u].z < S;
       o[u] = Vox4<T>{};
       if (!on[u]) continue;
-      const T* p = src + ((int64_t)w[u].z * S + w[u].y) * S + w[u].x;
+      const T* from = src + ((int64_t)w[u].z * S + w[u].y) * S + w[u].x;
       if (WIDE) {
-        const uint32_t* q = reinterpret_cast<const uint32_t*>(p);
+        const uint32_t* q = reinterpret_cast<const uint32_t*>(from);
         if (w[u].x < S) o[u].w[0] = q[0];
         if (w[u].x + 2 < S) o[u].w[sizeof(T) - 1] = q[1];
       } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          if (w[u].x + k < S) o[u].set(k, p[k]);
+          if (w[u].x + k < S) o[u].set(k, from[k]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) {
-      const int i = i0 + 256 * u + (int)threadIdx.x;
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + 256 * u + p.lane;
       uint32_t rmax = 0u;
       if (on[u]) {
         row_range(o[u], S - w[u].x, lo, rmax);
         store_row<T, MB>(dst, w[u], i, S, Sx, o[u]);
       }
       hi = max(hi, rmax);
+      if (PACK) continue;  // (no block maxima)
       rmax = row16_max(rmax);
       if (bm && i < items && (i & 15) == 0) bm[i >> 4] = (T)rmax;
     }
   }
-  range_out(lo, hi, range + 2 * (int64_t)entries[j], per == 1);
+  range_out<PACK>(lo, hi, any ? range + 2 * (int64_t)entries[j] : nullptr, per == 1, p);
 }
 
 // The small tables of a put: a freshly stored brick counts as used now
@@ -207,20 +211,21 @@ sg_status send_regions(Volume* v, int64_t region, int64_t b0, int64_t k, const v
 // Store the regions at dsrc in their slots.
 void launch_put(Volume* v, int n, const int32_t* d_slot, const int32_t* d_ent, const void* dsrc,
                 hipStream_t s) {
-  const int per = groups_per_brick(n, v->Mb * v->Mb * v->Mb * 16);
-  const dim3 grid((unsigned)((int64_t)n * per));
+  const Shares sh = brick_shares(n, v->Mb);
   const bool wide = v->bpv == 2 && reinterpret_cast<uintptr_t>(dsrc) % 4 == 0;
-#define SG_PUT(T, MB, WIDE)                                                                    \
-  hipLaunchKernelGGL((put_kernel<T, MB, WIDE>), grid, dim3(256), 0, s, v->pool, v->slot_bytes, \
-                     d_slot, d_ent, (const T*)dsrc, v->range, v->bmax, v->bmax_stride, per, v->S,     \
-                     v->Sx, v->Mb)
-  if (v->bpv == 1) {
-    if (v->M) SG_PUT(uint8_t, true, false); else SG_PUT(uint8_t, false, false);
-  } else if (wide) {
-    if (v->M) SG_PUT(uint16_t, true, true); else SG_PUT(uint16_t, false, true);
-  } else {
-    if (v->M) SG_PUT(uint16_t, true, false); else SG_PUT(uint16_t, false, false);
-  }
+#define SG_PUT(T, MB, WIDE, PACK)                                                              \
+  hipLaunchKernelGGL((put_kernel<T, MB, WIDE, PACK>), dim3(sh.grid), dim3(256), 0, s, v->pool, \
+                     v->slot_bytes, d_slot, d_ent, (const T*)dsrc, v->range, v->bmax,          \
+                     v->bmax_stride, sh.n, sh.per, v->S, v->Sx, v->Mb)
+#define SG_PUT_W(T, WIDE)                                                                      \
+  do {                                                                                         \
+    if (v->M) { if (sh.pack) SG_PUT(T, true, WIDE, true); else SG_PUT(T, true, WIDE, false); } \
+    else { if (sh.pack) SG_PUT(T, false, WIDE, true); else SG_PUT(T, false, WIDE, false); }    \
+  } while (0)
+  if (v->bpv == 1) SG_PUT_W(uint8_t, false);
+  else if (wide) SG_PUT_W(uint16_t, true);
+  else SG_PUT_W(uint16_t, false);
+#undef SG_PUT_W
 #undef SG_PUT
   launch_dark(v, n, d_slot, d_ent, v->dark, s);
 }

@@ -50,58 +50,61 @@ __device__ __forceinline__ bool core_row(const Row& w, int B) {
 }
 
 // Upload: scatter n brick cores (x fastest) into their slots, one thread per
-// stored row of four voxels (see brick_rows.h); workgroup blockIdx.x serves
-// brick blockIdx.x / per. Bound by memory. A stored row holds core voxels
-// x - 1 .. x + 2 (x a multiple of four): WIDE reads the aligned voxels
+// stored row of four voxels (see brick_rows.h). Bound by memory. A stored row
+// holds core voxels x - 1 .. x + 2 (x a multiple of four): WIDE reads the aligned voxels
 // x .. x + 3 with one load and voxel x - 1 with another (cores of at least
 // four voxels an edge at a row-aligned address); otherwise voxel by voxel.
 // 512^3 uint16 in micro-block slots: 167 us (3.2 TB/s read and written; 426
 // with one thread per voxel, 260 with one row in flight and 2-byte loads).
-template <typename T, bool MB, bool WIDE>
+template <typename T, bool MB, bool WIDE, bool PACK>
 __global__ __launch_bounds__(256) void upload_kernel(uint8_t* __restrict__ pool,
                                                      int64_t slot_bytes, const int32_t* page,
                                                      LevelGeom lg, const int32_t* coords,
-                                                     const T* __restrict__ src, int per, int logB,
-                                                     int S, int Sx, int M) {
-  const int j = (int)(blockIdx.x / (unsigned)per), part = (int)(blockIdx.x % (unsigned)per);
+                                                     const T* __restrict__ src, int n, int per,
+                                                     int logB, int S, int Sx, int M) {
+  constexpr int kBatch = PACK ? 1 : kRowBatch;
   const int B = 1 << logB, items = M * M * M * 16;
+  const Part p = brick_part<PACK, true>(per, M);
+  const int64_t j = p.j;
+  if (j >= n) return;
   const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_mm = __builtin_amdgcn_rcpf((float)(M * M));
   const int32_t* c = coords + 3 * (int64_t)j;
   const int64_t node = lg.node_off + ((int64_t)c[2] * lg.g[1] + c[1]) * lg.g[0] + c[0];
   T* dst = slot_ptr<T>(pool, slot_bytes, page[node]);
-  src += (int64_t)j << (3 * logB);
-  for (int i0 = part * 256 * kRowBatch + (int)threadIdx.x; i0 < items; i0 += per * 256 * kRowBatch) {
-    Row w[kRowBatch];
-    Vox4<T> o[kRowBatch];
-    uint32_t before[kRowBatch];
-    bool on[kRowBatch];
+  src += j << (3 * logB);
+  const int first = PACK ? core_row_number(p.lane, M) : p.part * 256 * kBatch + p.lane;
+  for (int i0 = first; i0 < items; i0 += PACK ? items : per * 256 * kBatch) {
+    Row w[kBatch];
+    Vox4<T> o[kBatch];
+    uint32_t before[kBatch];
+    bool on[kBatch];
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) {
+    for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + 256 * u;
       w[u] = row_at(i, M, inv_m, inv_mm);
       on[u] = i < items && core_row(w[u], B);
       if (!on[u]) continue;
-      const T* p = src + ((((w[u].z - 1) << logB) + (w[u].y - 1)) << logB);
+      const T* q = src + ((((w[u].z - 1) << logB) + (w[u].y - 1)) << logB);
       const int x = w[u].x;
       if (WIDE) {
         o[u] = Vox4<T>{};
         if (x < B) {
           if (sizeof(T) == 1) {
-            o[u].w[0] = *reinterpret_cast<const uint32_t*>(p + x);
+            o[u].w[0] = *reinterpret_cast<const uint32_t*>(q + x);
           } else {
-            const uint2 ab = *reinterpret_cast<const uint2*>(p + x);
+            const uint2 ab = *reinterpret_cast<const uint2*>(q + x);
             o[u].w[0] = ab.x;
             o[u].w[sizeof(T) - 1] = ab.y;
           }
         }
-        before[u] = p[max(x - 1, 0)];
+        before[u] = q[max(x - 1, 0)];
       } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) o[u].set(k, p[clampi(x + k - 1, 0, B - 1)]);
+        for (int k = 0; k < 4; ++k) o[u].set(k, q[clampi(x + k - 1, 0, B - 1)]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) {
+    for (int u = 0; u < kBatch; ++u) {
       if (!on[u]) continue;
       if (WIDE) {  // one voxel to the right
         if (sizeof(T) == 1) {
@@ -128,27 +131,29 @@ __global__ __launch_bounds__(256) void upload_kernel(uint8_t* __restrict__ pool,
 // beyond the core's end has one core voxel; the other three are apron.
 // Three levels of 512^3 uint16: 178 us (226 with a 2-byte load per child, 400
 // with one thread, eight node look-ups and 64-bit divisions per voxel).
-template <typename T, bool MB>
+template <typename T, bool MB, bool PACK>
 __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t slot_bytes,
                                                          const int32_t* page, LevelGeom src,
-                                                         LevelGeom dst, int per, int logB, int S,
-                                                         int Sx, int M) {
-  const int64_t j = blockIdx.x / (unsigned)per;
-  const int part = (int)(blockIdx.x % (unsigned)per);
+                                                         LevelGeom dst, int n, int per, int logB,
+                                                         int S, int Sx, int M) {
   const int B = 1 << logB, mask = B - 1, items = M * M * M * 16;
   const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_mm = __builtin_amdgcn_rcpf((float)(M * M));
-  const int b[3] = {(int)(j % dst.g[0]), (int)((j / dst.g[0]) % dst.g[1]),
-                    (int)(j / ((int64_t)dst.g[0] * dst.g[1]))};
+  const Part p = brick_part<PACK, true>(per, M);
+  const int64_t j = p.j;
+  const uint32_t row = (uint32_t)j / (uint32_t)dst.g[0];
+  const int b[3] = {(int)((uint32_t)j - row * (uint32_t)dst.g[0]), (int)(row % (uint32_t)dst.g[1]),
+                    (int)(row / (uint32_t)dst.g[1])};
   // the source slots under this brick (indices clamped into the grid: those
   // beyond it are never the brick of a child)
-  __shared__ int32_t slots[8];
-  if (threadIdx.x < 8) {
-    const int k = (int)threadIdx.x;
+  __shared__ int32_t under[kMostBricks<PACK, true>][8];
+  int32_t* const slots = under[p.sub];
+  for (int k = p.lane; k < 8 && j < n; k += p.threads) {
     const int sx = min(2 * b[0] + (k & 1), src.g[0] - 1), sy = min(2 * b[1] + ((k >> 1) & 1), src.g[1] - 1),
               sz = min(2 * b[2] + (k >> 2), src.g[2] - 1);
     slots[k] = page[src.node_off + ((int64_t)sz * src.g[1] + sy) * src.g[0] + sx];
   }
   __syncthreads();
+  if (j >= n) return;
   T* out = slot_ptr<T>(pool, slot_bytes, page[dst.node_off + j]);
   // the parts of slot_index per axis (stored index = core index + 1)
   auto fx = [&](int h) { const int x = (h & mask) + 1; return MB ? ((x >> 2) << 6) + (x & 3) : x; };
@@ -160,7 +165,8 @@ __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t 
     const int z = (h & mask) + 1;
     return MB ? (((z >> 2) * M * M) << 6) + ((z & 3) << 4) : z * S * Sx;
   };
-  for (int i = part * 256 + (int)threadIdx.x; i < items; i += per * 256) {
+  const int first = PACK ? core_row_number(p.lane, M) : p.part * 256 + p.lane;
+  for (int i = first; i < items; i += PACK ? items : per * 256) {
     const Row w = row_at(i, M, inv_m, inv_mm);
     if (!core_row(w, B)) continue;
     const int gy = min(b[1] * B + w.y - 1, dst.n[1] - 1), gz = min(b[2] * B + w.z - 1, dst.n[2] - 1);
@@ -173,31 +179,31 @@ __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t 
     auto one = [&](int k) {
       const int gx = min(b[0] * B + clampi(w.x + k - 1, 0, B - 1), dst.n[0] - 1);
       const int x0 = 2 * gx, x1 = min(2 * gx + 1, src.n[0] - 1);
-      const T* p = slot_ptr<T>(pool, slot_bytes, slots[oct | ((x0 >> logB) & 1)]);
+      const T* q = slot_ptr<T>(pool, slot_bytes, slots[oct | ((x0 >> logB) & 1)]);
       const int a = fx(x0), c = fx(x1);
-      const uint32_t sum = (uint32_t)p[r00 + a] + p[r00 + c] + p[r10 + a] + p[r10 + c] +
-                           p[r01 + a] + p[r01 + c] + p[r11 + a] + p[r11 + c];
+      const uint32_t sum = (uint32_t)q[r00 + a] + q[r00 + c] + q[r10 + a] + q[r10 + c] +
+                           q[r01 + a] + q[r01 + c] + q[r11 + a] + q[r11 + c];
       o.set(k, (sum + 4u) >> 3);
     };
     one(0);
     const int cx = b[0] * B + w.x;  // voxels 1 .. 3 are the level's cx .. cx + 2
     if (B >= 8 && w.x < B && 2 * cx + 5 < src.n[0]) {
       const int h = (2 * w.x) & mask;  // their children: stored h + 1 .. h + 6
-      const T* p = slot_ptr<T>(pool, slot_bytes, slots[oct | (((2 * cx) >> logB) & 1)]) +
+      const T* q = slot_ptr<T>(pool, slot_bytes, slots[oct | (((2 * cx) >> logB) & 1)]) +
                    (MB ? (h >> 2) << 6 : h);
       const int next = MB ? 64 : 4;
       const int rows[4] = {r00, r10, r01, r11};
-      Vox4<T> q[4][2];
+      Vox4<T> c[4][2];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) q[r][u] = four_at<T, MB>(p + rows[r] + u * next);
+        for (int u = 0; u < 2; ++u) c[r][u] = four_at<T, MB>(q + rows[r] + u * next);
       uint32_t s1 = 4u, s2 = 4u, s3 = 4u;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        s1 += q[r][0].get(1) + q[r][0].get(2);
-        s2 += q[r][0].get(3) + q[r][1].get(0);
-        s3 += q[r][1].get(1) + q[r][1].get(2);
+        s1 += c[r][0].get(1) + c[r][0].get(2);
+        s2 += c[r][0].get(3) + c[r][1].get(0);
+        s3 += c[r][1].get(1) + c[r][1].get(2);
       }
       o.set(1, s1 >> 3);
       o.set(2, s2 >> 3);
@@ -222,14 +228,14 @@ __global__ __launch_bounds__(256) void downsample_kernel(uint8_t* pool, int64_t 
 // us in one launch (332 in four, one thread walking the 66 voxels of each
 // stored row); fused with range_kernel the two took 221 us instead of 164:
 // most waves hold an apron row, so most paid for the fill.
-template <typename T, bool MB>
+template <typename T, bool MB, bool PACK>
 __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_bytes,
                                                     const int32_t* page, const NodeInfo* info,
-                                                    Levels lv, uint32_t* range, int per, int logB,
-                                                    int S, int Sx, int M) {
-  const int64_t node = blockIdx.x / (unsigned)per;
-  const int part = (int)(blockIdx.x % (unsigned)per);
-  const int B = 1 << logB, mask = B - 1;
+                                                    Levels lv, uint32_t* range, int n, int per,
+                                                    int logB, int S, int Sx, int M) {
+  const int B = 1 << logB, mask = B - 1, items = M * M * M * 16;
+  const Part p = brick_part<PACK>(per, M);
+  const int64_t node = min(p.j, (int64_t)n - 1);
   const NodeInfo ni = info[node];
   const int L = ni.level;
   const int n0 = lv.n[L][0], n1 = lv.n[L][1], n2 = lv.n[L][2];
@@ -237,16 +243,17 @@ __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_
   T* own = slot_ptr<T>(pool, slot_bytes, page[node]);
   // the slots of the 3x3x3 bricks around this one (clamped into the grid:
   // one beyond it never owns a clamped voxel)
-  __shared__ int32_t near[27];
-  if (threadIdx.x < 27) {
-    const int k = (int)threadIdx.x;
+  __shared__ int32_t around[kMostBricks<PACK>][27];
+  int32_t* const near = around[p.sub];
+  for (int k = p.lane; k < 27; k += p.threads) {
     const int x = clampi(ni.b[0] + k % 3 - 1, 0, lv.g[L][0] - 1),
               y = clampi(ni.b[1] + (k / 3) % 3 - 1, 0, lv.g[L][1] - 1),
               z = clampi(ni.b[2] + k / 9 - 1, 0, lv.g[L][2] - 1);
     near[k] = page[lv.node_off[L] + ((int64_t)z * lv.g[L][1] + y) * lv.g[L][0] + x];
   }
   __syncthreads();
-  if (part == 0 && threadIdx.x == 0) {
+  if (p.j >= n) return;
+  if (p.part == 0 && p.lane == 0) {
     range[2 * node] = 0xFFFFFFFFu;
     range[2 * node + 1] = 0u;
   }
@@ -262,7 +269,7 @@ __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_
   if (g0 + B < n0 && g1 + B < n1 && g2 + B < n2) {
     const int face = S * S;
     const float inv_f = __builtin_amdgcn_rcpf((float)face), inv_s = __builtin_amdgcn_rcpf((float)S);
-    for (int i = part * 256 + (int)threadIdx.x; i < 6 * face; i += per * 256) {
+    for (int i = p.part * 256 + p.lane; i < 6 * face; i += per * p.threads) {
       const int f = quot_exact(i, inv_f), r = i - f * face, v = quot_exact(r, inv_s), u = r - v * S;
       const int edge = (f & 1) ? S - 1 : 0;
       // faces 0, 1 across x, 2, 3 across y, 4, 5 across z; u runs along the
@@ -272,9 +279,8 @@ __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_
     }
     return;
   }
-  const int items = M * M * M * 16;
   const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_mm = __builtin_amdgcn_rcpf((float)(M * M));
-  for (int i = part * 256 + (int)threadIdx.x; i < items; i += per * 256) {
+  for (int i = p.part * 256 + p.lane; i < items; i += per * 256) {
     const Row w = row_at(i, M, inv_m, inv_mm);
     if (w.y >= S || w.z >= S) continue;
     const bool row_core = w.y >= 1 && w.y <= B && w.z >= 1 && w.z <= B && g1 + w.y < n1 &&
@@ -295,43 +301,47 @@ __global__ __launch_bounds__(256) void apron_kernel(uint8_t* pool, int64_t slot_
 // thread per stored row of four voxels; bound by reading the pool once.
 // Four levels of 512^3 uint16: 68 us (5.4 TB/s; 555 with one workgroup per
 // brick and a division per voxel); one 128^3 uint8 brick took 3.1 ms so.
-template <typename T, bool MB>
+template <typename T, bool MB, bool PACK>
 __global__ __launch_bounds__(256) void range_kernel(const uint8_t* __restrict__ pool,
                                                     int64_t slot_bytes, const int32_t* page,
                                                     uint32_t* range, uint8_t* bmax,
-                                                    int64_t bmax_stride, int per, int S, int Sx,
-                                                    int M) {
-  const int64_t node = blockIdx.x / (unsigned)per;
-  const int part = (int)(blockIdx.x % (unsigned)per), items = M * M * M * 16;
+                                                    int64_t bmax_stride, int n, int per, int S,
+                                                    int Sx, int M) {
+  constexpr int kBatch = PACK ? 1 : kRowBatch;
+  const int items = M * M * M * 16;
+  const Part p = brick_part<PACK>(per, M);
+  const bool any = !PACK || p.j < n;
+  const int64_t node = any ? p.j : 0;
   const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_mm = __builtin_amdgcn_rcpf((float)(M * M));
   const int32_t slot = page[node];
   const T* own = reinterpret_cast<const T*>(pool + (int64_t)slot * slot_bytes);
   T* bm = bmax ? reinterpret_cast<T*>(bmax + (int64_t)slot * bmax_stride) : nullptr;
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   // (the same trip count for every lane: blocks are folded across lanes)
-  for (int i0 = part * 256 * kRowBatch; i0 < items; i0 += per * 256 * kRowBatch) {
-    Row w[kRowBatch];
-    Vox4<T> o[kRowBatch];
-    bool on[kRowBatch];
+  for (int i0 = p.part * 256 * kBatch; i0 < items; i0 += per * 256 * kBatch) {
+    Row w[kBatch];
+    Vox4<T> o[kBatch];
+    bool on[kBatch];
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) {
-      const int i = i0 + 256 * u + (int)threadIdx.x;
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + 256 * u + p.lane;
       w[u] = row_at(i, M, inv_m, inv_mm);
-      on[u] = i < items && w[u].y < S && w[u].z < S;
+      on[u] = any && i < items && w[u].y < S && w[u].z < S;
       o[u] = Vox4<T>{};
       if (on[u]) o[u] = load_row<T, MB>(own, w[u], i, S, Sx);
     }
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) {
-      const int i = i0 + 256 * u + (int)threadIdx.x;
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = i0 + 256 * u + p.lane;
       uint32_t rmax = 0u;
       if (on[u]) row_range(o[u], S - w[u].x, lo, rmax);
       hi = max(hi, rmax);
+      if (PACK) continue;  // (no block maxima)
       rmax = row16_max(rmax);
       if (bm && i < items && (i & 15) == 0) bm[i >> 4] = (T)rmax;
     }
   }
-  range_out(lo, hi, range + 2 * node, per == 1);
+  range_out<PACK>(lo, hi, any ? range + 2 * node : nullptr, per == 1, p);
 }
 
 // Of a brick's regions of three to four blocks an edge, about the size of a
@@ -455,50 +465,57 @@ const int32_t* page_at(const Volume* v, int c, int t) {
   return v->page + ((int64_t)t * v->d.channels + c) * v->nodes;
 }
 
-int rows_per_brick(const Volume* v) { return v->Mb * v->Mb * v->Mb * 16; }
-
 }  // namespace
 
 sg_status launch_upload(Volume* v, int c, int t, int level, int n,
                         const int32_t* dcoords, const void* dsrc,
                         hipStream_t s) {
   const LevelGeom lg = geom(v, level);
-  const int per = groups_per_brick(n, rows_per_brick(v));
-  const dim3 grid((unsigned)((int64_t)n * per));
+  const Shares sh = brick_shares(n, v->Mb, true);
   const bool wide = v->B >= 4 && reinterpret_cast<uintptr_t>(dsrc) % (4 * v->bpv) == 0;
-#define SG_UPLOAD(T, MB, WIDE)                                                                 \
-  hipLaunchKernelGGL((upload_kernel<T, MB, WIDE>), grid, dim3(256), 0, s, v->pool,             \
-                     v->slot_bytes, page_at(v, c, t), lg, dcoords, (const T*)dsrc, per,        \
-                     v->logB, v->S, v->Sx, v->Mb)
-#define SG_UPLOAD_T(T)                                                       \
-  do {                                                                       \
-    if (v->M) {                                                              \
-      if (wide) SG_UPLOAD(T, true, true); else SG_UPLOAD(T, true, false);    \
-    } else {                                                                 \
-      if (wide) SG_UPLOAD(T, false, true); else SG_UPLOAD(T, false, false);  \
-    }                                                                        \
+#define SG_UPLOAD(T, MB, WIDE, PACK)                                                           \
+  hipLaunchKernelGGL((upload_kernel<T, MB, WIDE, PACK>), dim3(sh.grid), dim3(256), 0, s,       \
+                     v->pool, v->slot_bytes, page_at(v, c, t), lg, dcoords, (const T*)dsrc,    \
+                     sh.n, sh.per, v->logB, v->S, v->Sx, v->Mb)
+#define SG_UPLOAD_W(T, MB, WIDE) \
+  do { if (sh.pack) SG_UPLOAD(T, MB, WIDE, true); else SG_UPLOAD(T, MB, WIDE, false); } while (0)
+#define SG_UPLOAD_T(T)                                                           \
+  do {                                                                           \
+    if (v->M) {                                                                  \
+      if (wide) SG_UPLOAD_W(T, true, true); else SG_UPLOAD_W(T, true, false);    \
+    } else {                                                                     \
+      if (wide) SG_UPLOAD_W(T, false, true); else SG_UPLOAD_W(T, false, false);  \
+    }                                                                            \
   } while (0)
   if (v->bpv == 1) SG_UPLOAD_T(uint8_t); else SG_UPLOAD_T(uint16_t);
 #undef SG_UPLOAD_T
+#undef SG_UPLOAD_W
 #undef SG_UPLOAD
   SG_HIP(hipGetLastError());
   return SG_OK;
 }
 
+// A statement for the volume's voxel type T, slot layout MB and sharing PACK.
+#define SG_BRICKS(STATEMENT)                                                                   \
+  do {                                                                                         \
+    if (v->bpv == 1) {                                                                         \
+      if (v->M) { if (sh.pack) STATEMENT(uint8_t, true, true); else STATEMENT(uint8_t, true, false); }       \
+      else { if (sh.pack) STATEMENT(uint8_t, false, true); else STATEMENT(uint8_t, false, false); }          \
+    } else {                                                                                   \
+      if (v->M) { if (sh.pack) STATEMENT(uint16_t, true, true); else STATEMENT(uint16_t, true, false); }     \
+      else { if (sh.pack) STATEMENT(uint16_t, false, true); else STATEMENT(uint16_t, false, false); }        \
+    }                                                                                          \
+  } while (0)
+
 sg_status launch_downsample(Volume* v, int c, int t, int level_dst,
                             hipStream_t s) {
   const LevelGeom src = geom(v, level_dst - 1), dst = geom(v, level_dst);
-  const int64_t bricks = (int64_t)dst.g[0] * dst.g[1] * dst.g[2];
-  const int per = groups_per_brick(bricks, rows_per_brick(v));
-  const dim3 grid((unsigned)(bricks * per));
-#define SG_DOWN(T, MB)                                                                          \
-  hipLaunchKernelGGL((downsample_kernel<T, MB>), grid, dim3(256), 0, s, v->pool, v->slot_bytes, \
-                     page_at(v, c, t), src, dst, per, v->logB, v->S, v->Sx, v->Mb)
-  if (v->bpv == 1) {
-    if (v->M) SG_DOWN(uint8_t, true); else SG_DOWN(uint8_t, false);
-  } else {
-    if (v->M) SG_DOWN(uint16_t, true); else SG_DOWN(uint16_t, false);
-  }
+  const Shares sh = brick_shares((int64_t)dst.g[0] * dst.g[1] * dst.g[2], v->Mb, true);
+#define SG_DOWN(T, MB, PACK)                                                                   \
+  hipLaunchKernelGGL((downsample_kernel<T, MB, PACK>), dim3(sh.grid), dim3(256), 0, s, v->pool, \
+                     v->slot_bytes, page_at(v, c, t), src, dst, sh.n, sh.per, v->logB, v->S,   \
+                     v->Sx, v->Mb)
+  SG_BRICKS(SG_DOWN);
 #undef SG_DOWN
   SG_HIP(hipGetLastError());
   return SG_OK;
@@ -515,21 +532,19 @@ sg_status launch_commit(Volume* v, int c, int t, hipStream_t s) {
     }
     lv.node_off[L] = v->node_off[L];
   }
-  const int per = groups_per_brick(v->nodes, rows_per_brick(v));
-  const dim3 grid((unsigned)(v->nodes * per));
-#define SG_COMMIT(T, MB)                                                                       \
+  const Shares sh = brick_shares(v->nodes, v->Mb);
+#define SG_COMMIT(T, MB, PACK)                                                                 \
   do {                                                                                         \
-    hipLaunchKernelGGL((apron_kernel<T, MB>), grid, dim3(256), 0, s, v->pool, v->slot_bytes,   \
-                       page_at(v, c, t), v->info, lv, r, per, v->logB, v->S, v->Sx, v->Mb);    \
-    hipLaunchKernelGGL((range_kernel<T, MB>), grid, dim3(256), 0, s, v->pool, v->slot_bytes,   \
-                       page_at(v, c, t), r, v->bmax, v->bmax_stride, per, v->S, v->Sx, v->Mb); \
+    hipLaunchKernelGGL((apron_kernel<T, MB, PACK>), dim3(sh.grid), dim3(256), 0, s, v->pool,   \
+                       v->slot_bytes, page_at(v, c, t), v->info, lv, r, sh.n, sh.per, v->logB, \
+                       v->S, v->Sx, v->Mb);                                                    \
+    hipLaunchKernelGGL((range_kernel<T, MB, PACK>), dim3(sh.grid), dim3(256), 0, s, v->pool,   \
+                       v->slot_bytes, page_at(v, c, t), r, v->bmax, v->bmax_stride, sh.n,      \
+                       sh.per, v->S, v->Sx, v->Mb);                                            \
   } while (0)
-  if (v->bpv == 1) {
-    if (v->M) SG_COMMIT(uint8_t, true); else SG_COMMIT(uint8_t, false);
-  } else {
-    if (v->M) SG_COMMIT(uint16_t, true); else SG_COMMIT(uint16_t, false);
-  }
+  SG_BRICKS(SG_COMMIT);
 #undef SG_COMMIT
+#undef SG_BRICKS
   launch_dark(v, (int)v->nodes, page_at(v, c, t), nullptr, v->dark + first, s);
   SG_HIP(hipGetLastError());
   return SG_OK;
