@@ -518,7 +518,8 @@ sg_status sg_pyramid_level(int32_t dtype, const int32_t src_dims[3], const void 
  *   out   : device buffer of n (brick+2)^3 voxels, caller-owned
  * n = 0 does nothing. Errors: SG_ERR_INVALID_ARG (NULL pointer, bad dtype,
  * dims or brick, n < 0, a coordinate outside the grid),
- * SG_ERR_DEVICE. */
+ * SG_ERR_OUT_OF_MEMORY / SG_ERR_DEVICE (the coordinates of thousands of
+ * small bricks are copied to the device). */
 sg_status sg_brick_regions(int32_t dtype, const int32_t dims[3], const void *level,
                            int32_t brick, int32_t n, const int32_t *coords, void *out,
                            void *hip_stream);

@@ -9,6 +9,7 @@
 // current device.
 #include <algorithm>
 #include <type_traits>
+#include <vector>
 
 #include "brick_rows.h"
 
@@ -111,22 +112,57 @@ struct BrickList {
 };
 constexpr int kQuads = 4;
 
+uint64_t pack_brick(const int32_t* c) {
+  return (uint64_t)c[0] | ((uint64_t)c[1] << 21) | ((uint64_t)c[2] << 42);
+}
+// Stored voxel (0, 0, 0) of a packed brick (coordinates below 2^20, see
+// check_dims).
+__device__ __forceinline__ void brick_origin(uint64_t packed, int B, int& g0, int& g1, int& g2) {
+  g0 = B * (int)(packed & 0x1FFFFF) - 1;
+  g1 = B * (int)((packed >> 21) & 0x1FFFFF) - 1;
+  g2 = B * (int)(packed >> 42) - 1;
+}
+// Four voxels of a level's row of n0 from voxel gx on, indices clamped.
+template <typename T>
+__device__ __forceinline__ void read_quad(const T* row, int gx, int n0, uint32_t (&v)[4]) {
+  // (any alignment: the compiler picks the load from it)
+  typedef T Quad __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  if (gx >= 0 && gx + 4 <= n0) {
+    const Quad q = *reinterpret_cast<const Quad*>(row + gx);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = q[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = row[min(max(gx + k, 0), n0 - 1)];
+  }
+}
+// ... stored, the first two of them at the end of a row of 4 q + 2.
+template <typename T>
+__device__ __forceinline__ void store_quad(T* o, const uint32_t (&v)[4], bool two) {
+  typedef T Quad __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  if (!two) {
+    Quad q;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = (T)v[k];
+    *reinterpret_cast<Quad*>(o) = q;
+  } else {
+    o[0] = (T)v[0];
+    o[1] = (T)v[1];
+  }
+}
+
 template <typename T, bool SMALL>
 __global__ __launch_bounds__(256) void region_kernel(const T* __restrict__ level, Dims d,
                                                      BrickList list, int n, int B, int per,
                                                      T* __restrict__ out) {
-  // (any alignment: the compiler picks the load from it)
-  typedef T Quad __attribute__((ext_vector_type(4), aligned(sizeof(T))));
   // workgroup w runs on XCD w % 8: the same rows of eight consecutive bricks
   // (neighbours in x, as a rule) are taken by one XCD in turn
   const int turn = (int)(blockIdx.x >> 3), unit = (turn >> 3) * 8 + (int)(blockIdx.x & 7);
   const int j = (unit / per) * 8 + (turn & 7), part = unit % per;
   if (j >= n) return;
   const int S = B + 2, quads = (S + 3) / 4, rows = S * S;
-  const uint64_t packed = list.b[j];
-  // stored voxel (0, 0, 0) of the brick (coordinates below 2^20, see check_dims)
-  const int g0 = B * (int)(packed & 0x1FFFFF) - 1, g1 = B * (int)((packed >> 21) & 0x1FFFFF) - 1,
-            g2 = B * (int)(packed >> 42) - 1;
+  int g0, g1, g2;
+  brick_origin(list.b[j], B, g0, g1, g2);
   const int n0 = (int)d.n[0], n1 = (int)d.n[1], n2 = (int)d.n[2];
   const int zb = max(g2, 0);  // (a brick's core starts inside the level)
   const T* base = level + (int64_t)zb * n1 * n0;
@@ -154,30 +190,60 @@ __global__ __launch_bounds__(256) void region_kernel(const T* __restrict__ level
           row = base + __umul24(__umul24(gz, n1) + gy, n0);
         else
           row = base + ((int64_t)gz * n1 + gy) * n0;
-        const int gx = g0 + x;
-        if (gx >= 0 && gx + 4 <= n0) {
-          const Quad q = *reinterpret_cast<const Quad*>(row + gx);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) v[u][k] = q[k];
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) v[u][k] = row[min(max(gx + k, 0), n0 - 1)];
-        }
+        read_quad(row, g0 + x, n0, v[u]);
       }
 #pragma unroll
       for (int u = 0; u < kQuads; ++u) {
         if (i0 + 256 * u >= items) break;
-        T* o = out + at[u];
-        if (!two[u]) {
-          Quad q;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) q[k] = (T)v[u][k];
-          *reinterpret_cast<Quad*>(o) = q;
-        } else {
-          o[0] = (T)v[u][0];
-          o[1] = (T)v[u][1];
-        }
+        store_quad(out + at[u], v[u], two[u]);
       }
+    }
+  }
+}
+
+// Many small bricks (of 2, 4 and 8): `group` consecutive ones to a workgroup,
+// about a thousand quads, their coordinates in device memory. A launch of 448
+// costs the host more than the device (512^3 uint16 in bricks of 8: 3461 us in
+// 586 launches, 1627 in one; 2026 with one thread per voxel), and a
+// brick of 2 has 16 quads for a workgroup's 256 threads. Eight workgroups in a
+// row run on one XCD, whose L2 holds the lines that neighbours in x share.
+// SMALL: the level's rows and voxels are counted in 24 and 31 bits.
+template <typename T, bool SMALL>
+__global__ __launch_bounds__(256) void region_group_kernel(const T* __restrict__ level, Dims d,
+                                                           const uint64_t* __restrict__ list,
+                                                           int n, int B, int group,
+                                                           T* __restrict__ out) {
+  const int w = (int)blockIdx.x, g = (w & ~63) | ((w & 7) << 3) | ((w >> 3) & 7);
+  const int64_t j0 = (int64_t)g * group;
+  if (j0 >= n) return;
+  const int here = (int)min((int64_t)group, n - j0);
+  const int S = B + 2, quads = (S + 3) / 4, rows = S * S, per = rows * quads, items = here * per;
+  const int n0 = (int)d.n[0], n1 = (int)d.n[1], n2 = (int)d.n[2];
+  const float inv_p = __builtin_amdgcn_rcpf((float)per), inv_q = __builtin_amdgcn_rcpf((float)quads),
+              inv_s = __builtin_amdgcn_rcpf((float)S);
+  out += j0 * rows * S;
+  for (int i0 = threadIdx.x; i0 < items; i0 += 256 * kQuads) {
+    uint32_t v[kQuads][4];
+    int at[kQuads];
+    bool two[kQuads];
+#pragma unroll
+    for (int u = 0; u < kQuads; ++u) {
+      const int i = min(i0 + 256 * u, items - 1);
+      const int b = quot_exact(i, inv_p), k = i - b * per, r = quot_exact(k, inv_q),
+                x = 4 * (k - r * quads), z = quot_exact(r, inv_s), y = r - z * S;
+      int g0, g1, g2;
+      brick_origin(list[j0 + b], B, g0, g1, g2);
+      const int gy = min(max(g1 + y, 0), n1 - 1), gz = min(max(g2 + z, 0), n2 - 1);
+      at[u] = (b * rows + r) * S + x;
+      two[u] = x + 2 >= S;
+      const T* row = SMALL ? level + __umul24(__umul24(gz, n1) + gy, n0)
+                           : level + ((int64_t)gz * n1 + gy) * n0;
+      read_quad(row, g0 + x, n0, v[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kQuads; ++u) {
+      if (i0 + 256 * u >= items) break;
+      store_quad(out + at[u], v[u], two[u]);
     }
   }
 }
@@ -195,6 +261,35 @@ sg_status check_dims(const int32_t* dims, const char* where) {
   for (int a = 0; a < 3; ++a)
     if (dims[a] < 1 || dims[a] > (1 << 20))
       return fail(SG_ERR_INVALID_ARG, std::string(where) + ": dims must be in [1, 2^20]");
+  return SG_OK;
+}
+
+// One launch of region_group_kernel over all n bricks.
+sg_status group_regions(int32_t dtype, Dims d, const void* level, int32_t brick, int32_t n,
+                        const int32_t* coords, void* out, hipStream_t s) {
+  std::vector<uint64_t> packed((size_t)n);
+  for (int32_t i = 0; i < n; ++i) packed[(size_t)i] = pack_brick(coords + 3 * (int64_t)i);
+  uint64_t* list = nullptr;
+  SG_HIP(hipMallocAsync((void**)&list, packed.size() * 8, s));
+  hipError_t e = hipMemcpyAsync(list, packed.data(), packed.size() * 8, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);  // the copy has read `packed`
+  if (e == hipSuccess) {
+    const bool small = d.n[1] * d.n[2] < (1 << 24) && d.n[0] < (1 << 24) &&
+                       d.n[0] * d.n[1] * d.n[2] < ((int64_t)1 << 31);
+    const void* k = dtype == SG_U8
+                        ? (small ? reinterpret_cast<const void*>(region_group_kernel<uint8_t, true>)
+                                 : reinterpret_cast<const void*>(region_group_kernel<uint8_t, false>))
+                        : (small ? reinterpret_cast<const void*>(region_group_kernel<uint16_t, true>)
+                                 : reinterpret_cast<const void*>(region_group_kernel<uint16_t, false>));
+    const int S = brick + 2;
+    int group = 1024 / (S * S * ((S + 3) / 4)) + 1, nb = n;
+    const int64_t groups = ((int64_t)n + group - 1) / group;
+    void* pa[] = {&level, &d, &list, &nb, &brick, &group, &out};
+    e = hipLaunchKernel(k, dim3((unsigned)((groups + 63) / 64 * 64)), dim3(256), pa, 0, s);
+  }
+  const hipError_t f = hipFreeAsync(list, s);
+  SG_HIP(e);
+  SG_HIP(f);
   return SG_OK;
 }
 
@@ -272,13 +367,19 @@ extern "C" sg_status sg_brick_regions(int32_t dtype, const int32_t dims[3], cons
                               : reinterpret_cast<const void*>(region_kernel<uint8_t, false>))
                      : (small ? reinterpret_cast<const void*>(region_kernel<uint16_t, true>)
                               : reinterpret_cast<const void*>(region_kernel<uint16_t, false>));
+  // From seven launches on, small bricks go in one, with a copy of their
+  // coordinates and a wait for it (about 50 us; a launch 11 us), unless the
+  // stream is being captured.
+  if (brick <= 8 && n > 7 * kLaunchBricks) {
+    hipStream_t s = (hipStream_t)hip_stream;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap == hipStreamCaptureStatusNone) return group_regions(dtype, d, level, brick, n, coords, out, s);
+  }
   BrickList list;
   for (int32_t i0 = 0; i0 < n; i0 += kLaunchBricks) {
     const int m = std::min<int32_t>(kLaunchBricks, n - i0);
-    for (int i = 0; i < m; ++i) {
-      const int32_t* c = coords + 3 * (int64_t)(i0 + i);
-      list.b[i] = (uint64_t)c[0] | ((uint64_t)c[1] << 21) | ((uint64_t)c[2] << 42);
-    }
+    for (int i = 0; i < m; ++i) list.b[i] = pack_brick(coords + 3 * (int64_t)(i0 + i));
     int per = groups_per_brick(m, (int)(S * S * ((S + 3) / 4) * kRowBatch / kQuads));
     int nb = m;
     const int64_t units = (int64_t)((m + 7) / 8) * per;  // dealt to the XCDs in turn
