@@ -1,6 +1,7 @@
 """Brick regions where the route changes: thousands of small bricks (one
 launch over groups of them, coordinates in device memory; under capture the
-launches that carry them), against clamped indexing in numpy, and their cost."""
+launches that carry them), and levels whose rows or planes need 64-bit
+offsets, on both sides of each limit, against clamped indexing in numpy."""
 import numpy as np
 import pytest
 
@@ -74,6 +75,16 @@ def test_many_bricks_of_large_planes(dims, dtype):
     # rows of all planes: 2^24 - 4096 and 2^24 + 4096, and few
     lev, c = level(dims, dtype), some_bricks(dims, 8, 4000)
     assert np.array_equal(regions(lev, 8, c), expected(lev, 8, c))
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.uint16])
+@pytest.mark.parametrize("ny", [65027, 65029])
+def test_rows_beyond_24_bits(ny, dtype):
+    # a brick of 256 spans 258 planes: 258 ny rows, just below and above 2^24
+    dims = (2, ny, 2)
+    lev = level(dims, dtype)
+    c = np.array([[0, 0, 0], [0, 127, 0], [0, ny // 256 - 1, 0], [0, ny // 256, 0]], np.int32)
+    assert np.array_equal(regions(lev, 256, c), expected(lev, 256, c))
 
 
 def test_cost_of_many_small_bricks():
