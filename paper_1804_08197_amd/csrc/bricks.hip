@@ -25,13 +25,16 @@ struct Dims {
 // child index clamped to the finer level, + 4) >> 3 (the pyramid rule of
 // the resident volume's builder, on a linear array).
 //
-// Rows of dst are dealt to the workgroups in windows of `rows`; a thread
-// makes two voxels of a row (`half` = ceil(dst x / 2) of them to a row) from
-// four voxels of each of four source rows, one load a row where the four lie
-// in the level at an address aligned to them, else voxel by voxel. Bound by
-// reading the source once: three levels of 700x512x420 uint16 122 us.
+// A thread makes two voxels of a row from four voxels of each of four source
+// rows, one load a row where the four lie in the level at an address aligned
+// to them, else voxel by voxel. A workgroup takes `rows` rows of a piece of
+// `piece` pairs (`cols` pieces to a row): 2048 pairs, or fewer so that some
+// 2048 workgroups share a small level (whole rows in windows of 2048 pairs
+// left 100000x8x8 to 16 of them, 115 us against 14). Bound by reading the
+// source once: three levels of 700x512x420 uint16 122 us.
 template <typename T>
-__device__ __forceinline__ void four_voxels(const T* row, int64_t x, int64_t n, uint32_t (&v)[4]) {
+__device__ __forceinline__ void four_voxels(const T* row, int64_t x, int64_t n, bool wide,
+                                            uint32_t (&v)[4]) {
   const T* p = row + x;
   if (x + 4 <= n && (reinterpret_cast<uintptr_t>(p) & (4 * sizeof(T) - 1)) == 0) {
     if (sizeof(T) == 1) {
@@ -46,41 +49,52 @@ __device__ __forceinline__ void four_voxels(const T* row, int64_t x, int64_t n, 
       v[3] = a.y >> 16;
     }
   } else {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = row[min(x + k, n - 1)];
+    v[0] = row[min(x, n - 1)];
+    v[1] = row[min(x + 1, n - 1)];
+    v[2] = v[3] = 0u;
+    if (wide) {  // more than one voxel a row to make (the same in every thread)
+      v[2] = row[min(x + 2, n - 1)];
+      v[3] = row[min(x + 3, n - 1)];
+    }
   }
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void pyramid_level_kernel(const T* __restrict__ src, Dims s,
                                                             T* __restrict__ dst, Dims d, int rows,
-                                                            int half) {
-  const int64_t r0 = (int64_t)blockIdx.x * rows, all = d.n[1] * d.n[2];
-  const int here = (int)min((int64_t)rows, all - r0);
-  const float inv_h = __builtin_amdgcn_rcpf((float)half);
-  for (int i = threadIdx.x; i < here * half; i += 256) {
-    const int dr = quot_exact(i, inv_h);
-    const int64_t row = r0 + dr, x = 2 * (int64_t)(i - dr * half);
-    const int64_t z = row / d.n[1], y = row - z * d.n[1];
+                                                            int piece, int cols) {
+  const int64_t r0 = (int64_t)(blockIdx.x / (unsigned)cols) * rows, all = d.n[1] * d.n[2];
+  const int c0 = (int)(blockIdx.x % (unsigned)cols) * piece, half = (int)((d.n[0] + 1) / 2);
+  const int here = (int)min((int64_t)rows, all - r0), n1 = (int)d.n[1];
+  const bool wide = d.n[0] > 1;
+  const int64_t z0 = r0 / n1;  // of the window's first row
+  const int y0 = (int)(r0 - z0 * n1);
+  const float inv_p = __builtin_amdgcn_rcpf((float)piece), inv_y = __builtin_amdgcn_rcpf((float)n1);
+  for (int i = threadIdx.x; i < here * piece; i += 256) {
+    const int dr = quot_exact(i, inv_p), pair = c0 + i - dr * piece;
+    if (pair >= half) continue;
+    const int dz = quot_exact(y0 + dr, inv_y);
+    const int64_t row = r0 + dr, x = 2 * (int64_t)pair, z = z0 + dz, y = y0 + dr - dz * n1;
     const int64_t y1 = min(2 * y + 1, s.n[1] - 1), z1 = min(2 * z + 1, s.n[2] - 1);
     const T *a = src + (2 * z * s.n[1] + 2 * y) * s.n[0], *b = src + (2 * z * s.n[1] + y1) * s.n[0],
             *c = src + (z1 * s.n[1] + 2 * y) * s.n[0], *e = src + (z1 * s.n[1] + y1) * s.n[0];
+    const bool both = x + 1 < d.n[0];
     uint32_t va[4], vb[4], vc[4], ve[4];
-    four_voxels(a, 2 * x, s.n[0], va);
-    four_voxels(b, 2 * x, s.n[0], vb);
-    four_voxels(c, 2 * x, s.n[0], vc);
-    four_voxels(e, 2 * x, s.n[0], ve);
+    four_voxels(a, 2 * x, s.n[0], wide, va);
+    four_voxels(b, 2 * x, s.n[0], wide, vb);
+    four_voxels(c, 2 * x, s.n[0], wide, vc);
+    four_voxels(e, 2 * x, s.n[0], wide, ve);
     uint32_t o[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k)
       o[k] = (va[2 * k] + va[2 * k + 1] + vb[2 * k] + vb[2 * k + 1] + vc[2 * k] + vc[2 * k + 1] +
               ve[2 * k] + ve[2 * k + 1] + 4u) >> 3;
     T* q = dst + row * d.n[0] + x;
-    if (sizeof(T) == 2 && x + 1 < d.n[0] && (reinterpret_cast<uintptr_t>(q) & 3) == 0) {
+    if (sizeof(T) == 2 && both && (reinterpret_cast<uintptr_t>(q) & 3) == 0) {
       *reinterpret_cast<uint32_t*>(q) = o[0] | (o[1] << 16);
     } else {
       q[0] = (T)o[0];
-      if (x + 1 < d.n[0]) q[1] = (T)o[1];
+      if (both) q[1] = (T)o[1];
     }
   }
 }
@@ -323,11 +337,12 @@ extern "C" sg_status sg_pyramid_level(int32_t dtype, const int32_t src_dims[3], 
   // hold an earlier call's error)
   const void* sp = src;
   void* dp = dst;
-  // windows of about 2048 voxel pairs (eight per thread)
-  int half = (int)((d.n[0] + 1) / 2);
-  int rows = std::max(1, 2048 / half);
-  void* pa[] = {&sp, &s, &dp, &d, &rows, &half};
-  const int64_t groups = (d.n[1] * d.n[2] + rows - 1) / rows;
+  const int64_t half = (d.n[0] + 1) / 2, pairs = half * d.n[1] * d.n[2];
+  const int64_t window = std::min<int64_t>(2048, std::max<int64_t>(256, pairs / 2048));
+  int cols = (int)((half + window - 1) / window), piece = (int)((half + cols - 1) / cols);
+  int rows = (int)std::max<int64_t>(1, window / piece);
+  void* pa[] = {&sp, &s, &dp, &d, &rows, &piece, &cols};
+  const int64_t groups = (d.n[1] * d.n[2] + rows - 1) / rows * cols;
   const void* k = dtype == SG_U8 ? reinterpret_cast<const void*>(pyramid_level_kernel<uint8_t>)
                                  : reinterpret_cast<const void*>(pyramid_level_kernel<uint16_t>);
   SG_HIP(hipLaunchKernel(k, dim3((unsigned)groups), dim3(256), pa, 0, (hipStream_t)hip_stream));
