@@ -84,7 +84,6 @@ void free_all(Volume* v) {
   hipFree(v->pool);
   hipFree(v->page);
   hipFree(v->range);
-  hipFree(v->dark);
   if (v->bmax) hipFree(v->bmax);
   hipFree(v->empty);
   hipFree(v->info);
@@ -186,8 +185,7 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
   const int64_t tf_bytes = tf_layout(kMaxChannels, kMaxTfEntries).bytes;
   bool ok = alloc((void**)&v->pool, pool_bytes) &&
             alloc((void**)&v->page, v->entries * 4) &&
-            alloc((void**)&v->range, v->entries * 8) &&
-            alloc((void**)&v->dark, v->entries * 4) &&
+            alloc((void**)&v->range, v->entries * 12) &&
             alloc((void**)&v->empty, (int64_t)d->timepoints * nodes) &&
             alloc((void**)&v->info, nodes * (int64_t)sizeof(NodeInfo)) &&
             alloc((void**)&v->tf, tf_bytes);
@@ -207,13 +205,13 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
     return fail(SG_ERR_OUT_OF_MEMORY, "device allocation failed (cache tables)");
   }
   if (v->cache) v->req_list = v->req_count + kReqHead;
+  v->dark = v->range + 2 * v->entries;
   // the block maxima (1/64 or 1/32 of the pool) only speed renders up: a
   // volume that leaves no room for them goes without, as do small bricks
   v->bmax_stride = v->slot_bytes >> bmax_shift(v->M != 0);
   const int64_t bmax_bytes = v->slots * v->bmax_stride;
   if (dark_regions(v->Mb) > 1 && v->bmax_stride >= (int64_t)v->Mb * v->Mb * v->Mb * v->bpv &&
-      hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
-      (uint64_t)bmax_bytes + ((uint64_t)1 << 30) < free_b) {
+      v->bytes + (uint64_t)bmax_bytes + ((uint64_t)1 << 30) < free_b) {
     if (hipMalloc((void**)&v->bmax, (size_t)bmax_bytes) == hipSuccess) {
       v->bytes += (uint64_t)bmax_bytes;
     } else {
@@ -258,8 +256,7 @@ sg_status create(const sg_volume_desc* d, sg_volume** out) {
           n.b[2] = z;
         }
   hipError_t e = hipMemset(v->pool, 0, (size_t)pool_bytes);
-  if (e == hipSuccess) e = hipMemset(v->range, 0, (size_t)(v->entries * 8));
-  if (e == hipSuccess) e = hipMemset(v->dark, 0, (size_t)(v->entries * 4));
+  if (e == hipSuccess) e = hipMemset(v->range, 0, (size_t)(v->entries * 12));
   if (e == hipSuccess) e = hipMemset(v->empty, 0, (size_t)(d->timepoints * nodes));
   if (e == hipSuccess)
     e = hipMemcpy(v->page, page.data(), (size_t)v->entries * 4, hipMemcpyHostToDevice);

@@ -180,7 +180,8 @@ struct Volume {
                               // of a slot (blocks x fastest), or NULL
   int64_t bmax_stride = 0;    // bytes per slot of bmax (slot_bytes >> bmax_shift)
   uint32_t* dark = nullptr;   // [T][C][nodes] what a quarter of a brick's
-                              // regions stay at or below (see dark_kernel)
+                              // regions stay at or below (see dark_kernel),
+                              // in the same allocation as range
   uint8_t* empty = nullptr;   // [T][nodes] bit 0: every channel transparent,
                               // bit 1: every channel emits nothing, bits 2
                               // and 3: few regions of some channel are
