@@ -35,6 +35,9 @@ METRIC = "samples/s and stereo frames/s, plain vs learned-upsampler path at PSNR
 HBM_PEAK = 8.0e12            # bytes/s, MI355X HBM3E
 FP32_PEAK = 157.3e12         # FLOP/s, MI355X FP32 vector (packed FMA)
 VALU_LANE_PEAK = 256 * 4 * 16 * 2.4e9  # VALU lane operations/s (non-packed)
+# What every sample count of a line, and the ALU roofline made of it, holds.
+SAMPLES_COUNTED = ("every sample of every ray up to its termination, as the instrumented render "
+                   "takes them; the timed render steps over those of slabs that hold nothing")
 FLOP_PER_SAMPLE = 31         # algorithmic FLOP of one single-channel sample (see flop_per_sample)
 
 
@@ -244,7 +247,7 @@ def main():
            "unit": "GB/s", "traffic": traffic}
     hbm["frac"] = hbm["achieved"] / hbm["peak"]
     alu = {"bound": "alu", "achieved": flops_alg / ray_avg_s / 1e12, "peak": FP32_PEAK / 1e12,
-           "unit": "TFLOP/s", "traffic": traffic}
+           "unit": "TFLOP/s", "traffic": traffic, "samples_counted": SAMPLES_COUNTED}
     alu["frac"] = alu["achieved"] / alu["peak"]
     roof, other = (alu, hbm) if alu["frac"] >= hbm["frac"] else (hbm, alu)
     # the VALU lane-operation rate: samples x the measured lane operations
@@ -268,6 +271,7 @@ def main():
                       "width": 1440, "height": 1600,
                       "step_voxels": 0.5, "ert": 0.99, "lod_tau_px": 1.0, "skip_empty": True},
            "samples_per_frame": samples, "samples_per_s": samples * fps,
+           "samples_counted": SAMPLES_COUNTED,
            "raycast_kernel_ms": ray_ms / n_k, "cutmap_kernel_ms": cut_ms / n_k,
            "step_ms_median": float(np.median(step_ms)),
            "step_ms_p10": float(np.percentile(step_ms, 10)),
@@ -408,7 +412,8 @@ def timed_events(fn, steps, warmup):
 def rooflines(samples, flop, bytes_alg, kernel_s):
     """(dominant, other) of the FP32 ALU and HBM rooflines of one launch."""
     alu = {"bound": "alu", "achieved": samples * flop / kernel_s / 1e12,
-           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None}
+           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None,
+           "samples_counted": SAMPLES_COUNTED}
     hbm = {"bound": "hbm", "achieved": bytes_alg / kernel_s / 1e9, "peak": HBM_PEAK / 1e9,
            "unit": "GB/s", "traffic": None}
     for r in (alu, hbm):
@@ -618,7 +623,8 @@ def run_batched(args):
     ray_avg_s = ray_ms / n_k * 1e-3
     best_ms = min(eager_ms, graph_ms)
     alu = {"bound": "alu", "achieved": samples * FLOP_PER_SAMPLE / ray_avg_s / 1e12,
-           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None}
+           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None,
+           "samples_counted": SAMPLES_COUNTED}
     alu["frac"] = alu["achieved"] / alu["peak"]
     out = {"metric": "samples/s of a 64-view uneven batch in one call", "value": samples / (best_ms * 1e-3),
            "unit": "samples/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -974,7 +980,8 @@ def run_hmd(h, views, launch, args):
     base = res["emission_absorption"]
     alu = {"bound": "alu",
            "achieved": base["samples"] * FLOP_PER_SAMPLE / (base["raycast_kernel_ms"] * 1e-3) / 1e12,
-           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None}
+           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None,
+           "samples_counted": SAMPLES_COUNTED}
     alu["frac"] = alu["achieved"] / alu["peak"]
     out = {"metric": "stereo frames/s of the bricked frame under each HMD variant",
            "value": 1e3 * len(res) / total_ms, "unit": "stereo frames/s (mean over variants)",
@@ -1067,7 +1074,8 @@ def run_octants(h, views, launch, args):
     alu = {"bound": "alu",
            "achieved": octs[slow]["samples"] * FLOP_PER_SAMPLE
            / (octs[slow]["raycast_kernel_ms"] * 1e-3) / 1e12,
-           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None}
+           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None,
+           "samples_counted": SAMPLES_COUNTED}
     alu["frac"] = alu["achieved"] / alu["peak"]
     out = {"metric": "stereo frames/s of one GPU's octant share (slowest of eight)",
            "value": 1e3 / slow_ms, "unit": "stereo frames/s", "n_gpus": 1,
@@ -1198,7 +1206,8 @@ def run_stream(args):
     samples = stats["total_samples"]
     npix = sum(v["width"] * v["height"] for v in views)
     alu = {"bound": "alu", "achieved": samples * flop_per_sample(C) / ray_s / 1e12,
-           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None}
+           "peak": FP32_PEAK / 1e12, "unit": "TFLOP/s", "traffic": None,
+           "samples_counted": SAMPLES_COUNTED}
     alu["frac"] = alu["achieved"] / alu["peak"]
     hbm = {"bound": "hbm", "achieved": (stats["microblocks"] * 64 * 2 + npix * 16) / ray_s / 1e9,
            "peak": HBM_PEAK / 1e9, "unit": "GB/s", "traffic": None}
