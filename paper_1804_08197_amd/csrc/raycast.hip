@@ -238,8 +238,9 @@ int64_t hit_tiles(int n_views, const ViewDev* views) {
 //   blobs, bricks of 16: 512^3 6400 tiles 347 -> 346, 10000 424 -> 472
 //   blobs, bricks of 32: 512^3 10000 tiles 375 -> 354, 18906 516 -> 552
 //   opaque ball, bricks of 8: 512^3 4096 tiles 1291 -> 830, 10000 1218 -> 943
+// (floor: the table's smallest extinction)
 bool split_rays(const Volume* v, const sg_render_params* p, const LaunchConfig& cfg, float t_ert,
-                int64_t blocks, int64_t tiles) {
+                double floor, int64_t blocks, int64_t tiles) {
   if (!cfg.gather || cfg.persistent || v->d.channels != 1 ||
       p->model != SG_MODEL_EMISSION_ABSORPTION || !step_adds_up(p->step_voxels) ||
       !(t_ert < 1.0f) || (blocks << (2 * cfg.bt_log)) > 32768)
@@ -249,8 +250,8 @@ bool split_rays(const Volume* v, const sg_render_params* p, const LaunchConfig& 
   for (int i = 0; i < 3; ++i) edge = std::max(edge, hi[i] - lo[i]);
   const double step = p->step_voxels * (double)((int64_t)1 << p->lod_bias);
   double chain = edge / step;
-  if (v->tf_floor > 0.0 && t_ert > 0.0f)
-    chain = std::min(chain, 1.0 - std::log((double)t_ert) / (v->tf_floor * step));
+  if (floor > 0.0 && t_ert > 0.0f)
+    chain = std::min(chain, 1.0 - std::log((double)t_ert) / (floor * step));
   chain = std::min(chain, 12.0 * v->B / p->step_voxels);
   return (double)tiles <= ((p->flags & SG_LOD) ? 4.0 : 16.0) * chain &&
          (double)(blocks << (2 * cfg.bt_log)) <= 128.0 * chain;
@@ -319,7 +320,7 @@ void fill_args(const Volume* v, const sg_render_params* params, int n_views,
   a.ert = (float)params->ert_alpha;
   a.t_ert = ert_transmittance(a.ert);
   a.depth_alpha = (float)params->depth_alpha;
-  a.split = split_rays(v, params, cfg, a.t_ert, blocks, tiles) ? 1 : 0;
+  a.split = split_rays(v, params, cfg, a.t_ert, v->tf_floor, blocks, tiles) ? 1 : 0;
   a.model = params->model;
   if (a.skip_empty && step_adds_up(params->step_voxels) &&
       (params->model != SG_MODEL_EMISSION_ABSORPTION || clear_samples_idle(params, a.t_ert)))
@@ -863,9 +864,10 @@ sg_status add_node(hipGraph_t graph, Launch& l, hipGraphNode_t* dep, hipGraphNod
   return SG_OK;
 }
 
-// Four lanes to a ray for `tiles` tiles that meet the volume?
-bool graph_splits(const sg_render_graph* g, int64_t tiles) {
-  return split_rays(g->v, &g->params, g->cfg, ert_transmittance((float)g->params.ert_alpha),
+// Four lanes to a ray for `tiles` tiles that meet the volume and a table of
+// that smallest extinction?
+bool graph_splits(const sg_render_graph* g, int64_t tiles, double floor) {
+  return split_rays(g->v, &g->params, g->cfg, ert_transmittance((float)g->params.ert_alpha), floor,
                     g->blocks, tiles);
 }
 
@@ -932,7 +934,7 @@ extern "C" sg_status sg_render_graph_create(sg_volume* vol, int32_t n_views,
             g->tiles, &a);
   a.queue = g->queue;
   for (int k = 0; k < 2; ++k) {
-    if (k == 1 && !graph_splits(g, 0)) break;  // no pose ever asks for it
+    if (k == 1 && !graph_splits(g, 0, 0.0)) break;  // no pose or table ever asks for it
     RenderArgs ak = a;
     ak.split = k;
     if ((st = raycast_launch(v, ak, false, &ray)) != SG_OK) return bail(st);
@@ -986,7 +988,7 @@ extern "C" sg_status sg_render_graph_launch(sg_render_graph* g, void* hip_stream
   hipStream_t s = (hipStream_t)hip_stream;
   sg_status st = commit(v, s);
   if (st != SG_OK) return st;
-  SG_HIP(hipGraphLaunch(g->exec[g->exec[1] && graph_splits(g, g->tiles) ? 1 : 0], s));
+  SG_HIP(hipGraphLaunch(g->exec[g->exec[1] && graph_splits(g, g->tiles, v->tf_floor) ? 1 : 0], s));
   return SG_OK;
 }
 

@@ -154,7 +154,10 @@ __host__ __device__ constexpr int bmax_shift(bool micro) { return micro ? 6 : 5;
 // Regions to an edge of a slot of Mb blocks an edge that are looked at
 // together before slabs are tested (one: the brick, which is skipped as a
 // whole where it holds nothing).
-__host__ __device__ constexpr int dark_regions(int Mb) { return Mb < 5 ? 1 : (Mb + 1) / 3; }
+constexpr int kDarkRegions = 6;
+__host__ __device__ constexpr int dark_regions(int Mb) {
+  return Mb < 5 ? 1 : Mb < 17 ? (Mb + 1) / 3 : kDarkRegions;
+}
 
 struct Volume {
   sg_volume_desc d{};

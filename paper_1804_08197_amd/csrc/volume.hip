@@ -350,56 +350,57 @@ __global__ __launch_bounds__(256) void range_kernel(const uint8_t* __restrict__ 
 // the brick whether it holds anything. Where fewer regions are, asking costs
 // more than the slabs stepped over save (every fiftieth 4^3 block opaque, at
 // random, and a quarter of the regions free of them: 1431 us a frame without
-// asking, 1419 with; every tenth, none free: 1421 and 1544). One workgroup
-// per brick, or one wave for bricks of 16 and 32 (37449 of 16: 27 us; 145 with a
-// workgroup). Bound by latency: the block maxima are read once, all loads
-// together, and folded into the regions' in LDS; one wave searches them, a
-// ballot for every 64, without barriers.
+// asking, 1419 with; every tenth, none free: 1421 and 1544). It is a guess at
+// what pays and decides nothing else, so bricks of 128 and 256 are taken in
+// six regions to an edge and by every second and fourth row of blocks.
+// One workgroup per brick, or one wave for bricks of 16 and 32. Bound by
+// latency: the block maxima are read once, a round's loads together, and
+// folded into the regions' in LDS; one wave searches them, a ballot for every
+// 64, without barriers. 8 us for 585 bricks of 64, 27 for 37449 of 16.
 template <typename T>
-__global__ __launch_bounds__(256) void dark_kernel(const uint8_t* bmax, int64_t bmax_stride,
+__global__ __launch_bounds__(512) void dark_kernel(const uint8_t* bmax, int64_t bmax_stride,
                                                    const int32_t* slots, const int32_t* entries,
                                                    int count, int threads, int M, uint32_t* dark) {
   extern __shared__ uint32_t dark_smem[];  // the regions of each of the workgroup's bricks
+  constexpr int kLoads = 5;
   const int sub = (int)threadIdx.x / threads, tid = (int)threadIdx.x % threads;
-  const int j = (int)blockIdx.x * (256 / threads) + sub;
+  const int j = (int)(blockIdx.x * (blockDim.x / threads)) + sub;
   const T* bm = reinterpret_cast<const T*>(bmax + (int64_t)slots[min(j, count - 1)] * bmax_stride);
-  const uint32_t* words = reinterpret_cast<const uint32_t*>(bm);  // (4-byte aligned, as is their end)
-  constexpr int kPer = 4 / (int)sizeof(T), kLoads = 20 / kPer;    // a brick of 64: one round
-  const int G = dark_regions(M), n = G * G * G, blocks = M * M * M, nw = (blocks + kPer - 1) / kPer;
-  const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_mm = __builtin_amdgcn_rcpf((float)(M * M));
+  const int G = dark_regions(M), n = G * G * G;
+  const int every = (M + 16) / 17, my = (M + every - 1) / every, blocks = M * my * my;
+  const float inv_m = __builtin_amdgcn_rcpf((float)M), inv_p = __builtin_amdgcn_rcpf((float)(M * my));
   uint32_t* const top = dark_smem + sub * n;
   for (int r = tid; r < n; r += threads) top[r] = 0u;
   __syncthreads();
-  for (int i0 = tid; i0 < nw; i0 += threads * kLoads) {
-    uint32_t w[kLoads];
+  for (int i0 = tid; i0 < blocks; i0 += threads * kLoads) {
+    uint32_t v[kLoads];
+    int at[kLoads];
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) w[u] = words[min(i0 + threads * u, nw - 1)];
+    for (int u = 0; u < kLoads; ++u) {
+      const int i = min(i0 + threads * u, blocks - 1);
+      const int sz = quot_exact(i, inv_p), t = i - sz * M * my, sy = quot_exact(t, inv_m);
+      const int z = sz * every, y = sy * every, x = t - sy * M;
+      v[u] = bm[(z * M + y) * M + x];
+      auto part = [&](int c) { return quot_exact(c * G, inv_m); };  // region of block c of an axis
+      at[u] = (part(z) * G + part(y)) * G + part(x);
+    }
 #pragma unroll
     for (int u = 0; u < kLoads; ++u)
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int b = kPer * (i0 + threads * u) + k;
-        if (b >= blocks) continue;
-        const int bz = quot_exact(b, inv_mm), t = b - bz * M * M, by = quot_exact(t, inv_m),
-                  bx = t - by * M;
-        auto part = [&](int c) { return quot_exact(c * G, inv_m); };  // region of block c of an axis
-        atomicMax(top + (part(bz) * G + part(by)) * G + part(bx),
-                  (w[u] >> (8 * sizeof(T) * k)) & (sizeof(T) == 1 ? 0xFFu : 0xFFFFu));
-      }
+      if (i0 + threads * u < blocks) atomicMax(top + at[u], v[u]);
   }
   __syncthreads();
   if (tid >= 64 || j >= count) return;  // whole waves
   const int lane = tid, need = (n + 3) / 4;
-  uint32_t v[4];  // the first 256 regions
+  constexpr int kTops = (kDarkRegions * kDarkRegions * kDarkRegions + 63) / 64;
+  uint32_t v[kTops];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) v[k] = lane + 64 * k < n ? top[lane + 64 * k] : 0xFFFFFFFFu;
+  for (int k = 0; k < kTops; ++k) v[k] = lane + 64 * k < n ? top[lane + 64 * k] : 0xFFFFFFFFu;
   uint32_t lo = 0u, hi = sizeof(T) == 1 ? 255u : 65535u;
   while (lo < hi) {  // the same in every lane
     const uint32_t mid = (lo + hi) / 2;
     int c = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) c += __popcll(__ballot(v[k] <= mid));
-    for (int r = 256; r < n; r += 64) c += __popcll(__ballot(r + lane < n && top[min(r + lane, n - 1)] <= mid));
+    for (int k = 0; k < kTops; ++k) c += __popcll(__ballot(v[k] <= mid));
     if (c >= need) hi = mid; else lo = mid + 1;
   }
   if (lane == 0) dark[entries ? entries[j] : j] = lo;
@@ -553,14 +554,15 @@ sg_status launch_commit(Volume* v, int c, int t, hipStream_t s) {
 void launch_dark(Volume* v, int n, const int32_t* slots, const int32_t* entries, uint32_t* dark,
                  hipStream_t s) {
   if (!v->bmax) return;  // slabs are not tested
-  const int G = dark_regions(v->Mb), threads = v->Mb <= 9 ? 64 : 256, bricks = 256 / threads;
+  const int G = dark_regions(v->Mb), threads = v->Mb <= 9 ? 64 : 512,
+            bricks = v->Mb <= 9 ? 4 : 1;
   const dim3 grid((unsigned)((n + bricks - 1) / bricks));
-  const size_t lds = (size_t)bricks * G * G * G * 4;  // 42592 bytes at most (bricks of 256)
+  const size_t lds = (size_t)bricks * G * G * G * 4;
   if (v->bpv == 1)
-    hipLaunchKernelGGL(dark_kernel<uint8_t>, grid, dim3(256), lds, s, v->bmax, v->bmax_stride,
+    hipLaunchKernelGGL(dark_kernel<uint8_t>, grid, dim3(threads * bricks), lds, s, v->bmax, v->bmax_stride,
                        slots, entries, n, threads, v->Mb, dark);
   else
-    hipLaunchKernelGGL(dark_kernel<uint16_t>, grid, dim3(256), lds, s, v->bmax, v->bmax_stride,
+    hipLaunchKernelGGL(dark_kernel<uint16_t>, grid, dim3(threads * bricks), lds, s, v->bmax, v->bmax_stride,
                        slots, entries, n, threads, v->Mb, dark);
 }
 
