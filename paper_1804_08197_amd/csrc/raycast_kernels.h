@@ -792,12 +792,17 @@ __device__ __forceinline__ void mark_tile(const RenderArgs& a, const TileLane& t
 // shares an XCD, and the XCDs whose stripes cross the volume finish last (24
 // views: 230 us of work on the least, 340 on the most laden). There the eight
 // are turned so that it is (bx + 3 by) % 8, the densest spread of eight (as
-// far as the eight lie in one row). 2 x 1080x1200 (17 blocks a row) 617 ->
-// 539 us; 2 x 1024x900 (16) 2783 -> 2400; 2 x 512x512 (8) 553 -> 459; 24
-// views of 320..1100 pixels 459 -> 425. One less than a multiple mirrors one
-// more but measured the same either way (1440 pixels, 23 blocks: 2988 ->
-// 3044, 3777 -> 3735 us from two directions) and is left alone. Taking the
-// rows from the volume's middle outward cost more in the L2s (1438 -> 1555
+// far as the eight lie in one row). 2 x 1080x1200 (17 blocks a row, lens, ROI,
+// maximum intensity) 550 -> 514 and 580 -> 516 us from two directions; 24
+// views of 320..1100 pixels 511 -> 477 and 472 -> 442. It spreads the work at
+// the cost of neighbours in the L2s, so single frames lose too: over three
+// models, staged and gather, one and two views and three directions the time
+// is 0.42 to 0.96 of row-major order with blocks of 128 pixels, 0.45 to 1.14
+// with 64 (median 0.82 to 0.98; the worst a two-view gather frame of 17 blocks
+// a row) and 0.60 to 1.07 with 32 (0.95 to 1.00). One less than a multiple
+// mirrors one more but measured the same either way (1440 pixels, 23 blocks:
+// 2988 -> 3044, 3777 -> 3735 us from two directions) and is left alone. Taking
+// the rows from the volume's middle outward cost more in the L2s (1438 -> 1555
 // us) than it saved at the end.
 __device__ __forceinline__ int dealt_block(int first, int x, int blocks_x) {
   if (blocks_x < 8 || (blocks_x & 7) > 1) return first + x;

@@ -352,8 +352,11 @@ sg_status cutmap_run(const Volume* v, const ViewDev* dviews, int n_views, int bi
 // that kernel is bound by its vector instructions), several channels the
 // values alone: the staged kernel's workgroups per CU are then set by LDS,
 // and half the table makes room for one more (three channels of 256 entries
-// with 8 KiB of staging per wave: 56 -> 44 KiB, two -> three; stereo frame of
-// three-channel cells 4546 -> 3800 us).
+// with 8 KiB of staging per wave: 56 -> 44 KiB, two -> three; 2 x 1440x1600 of
+// three-channel cells 4063 -> 3339 us). Where room is not the limit the two
+// measure the same: choosing per launch (32 to 512 entries, two to four
+// channels, staged and gather) moved only gather frames of three channels and
+// 512 entries, 8605 -> 8034 us with pairs.
 __host__ __device__ constexpr bool tf_pairs(int channels) { return channels == 1; }
 __host__ __device__ constexpr int tf_lds_entries(int channels, int n) {
   return tf_pairs(channels) ? 2 * channels * n : channels * (n + 1);
