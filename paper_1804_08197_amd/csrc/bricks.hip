@@ -31,7 +31,7 @@ struct Dims {
 // `piece` pairs (`cols` pieces to a row): 2048 pairs, or fewer so that some
 // 2048 workgroups share a small level (whole rows in windows of 2048 pairs
 // left 100000x8x8 to 16 of them, 115 us against 14). Bound by reading the
-// source once: three levels of 700x512x420 uint16 122 us.
+// source once: three levels of 700x512x420 uint16 106 us (122 in whole rows).
 template <typename T>
 __device__ __forceinline__ void four_voxels(const T* row, int64_t x, int64_t n, bool wide,
                                             uint32_t (&v)[4]) {
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void pyramid_level_kernel(const T* __restrict_
 // Bound by memory. A row of 66 uint16 voxels is 132 bytes at an odd voxel,
 // so it pulls two or three 128-byte lines, which its neighbours in x need
 // too, so neighbouring bricks go to one XCD and its L2. 812 bricks of 64^3
-// uint16 (five launches): 266 us (740 with one thread and two 64-bit
+// uint16 (five launches): 239 us (740 with one thread and two 64-bit
 // divisions per voxel, plus a copy of the coordinates and a wait per call);
 // two voxels or eight to a thread ran at 272 and 410 us (a row of 66 leaves
 // an eight mostly outside).
