@@ -42,9 +42,9 @@ def test_scattered_blocks_cost_no_tests(layout, share):
         v = gen.view(gen.look_at(eye, (n / 2, n / 2, n / 2)), 1080, 1200, np.tan(np.radians(50)))
         img = [torch.empty(1200, 1080, 4, device="cuda") for _ in range(2)]
         sides = [lambda s=s: sg.sg_render_views(h, [v], {"skip_empty": s}, [img[s]]) for s in (0, 1)]
-        us = [median_us(s) for s in sides * 3]
+        us = [median_us(s) for s in sides * 5]
         print(share, us, flush=True)
-        assert min(us[1::2]) <= 1.03 * min(us[0::2]), us
+        assert min(us[1::2]) <= 1.035 * min(us[0::2]), us
         assert torch.equal(*img)
     finally:
         sg.sg_volume_destroy(h)
